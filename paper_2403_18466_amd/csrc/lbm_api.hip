@@ -18,6 +18,7 @@
 #include "kernels_ref.hpp"
 #include "lbm.h"
 #include "wide.hpp"
+#include "wide_adj16.hpp"
 #include "wide_bwd.hpp"
 
 #include <vector>
@@ -617,8 +618,12 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
     if (e == hipSuccess) e = hipMalloc(&ctx->wide_packed, (size_t)pbytes);
     if (e == hipSuccess)
       e = hipMemcpy(ctx->wide_idx, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice);
-    std::vector<int> bidx = cfg->lattice == LBM_D2Q9 ? wide_bwd_index<9>() : wide_bwd_index<19>();
-    const size_t bbytes = (size_t)WideBwd<9>::nw * eb + 4 * (size_t)WideBwd<9>::nb;
+    std::vector<int> bidx;
+    if (eb == 4)
+      bidx = cfg->lattice == LBM_D2Q9 ? wide_bwd_index<9>() : wide_bwd_index<19>();
+    else
+      bidx = cfg->lattice == LBM_D2Q9 ? wide_adj_index<9>() : wide_adj_index<19>();
+    const size_t bbytes = (bidx.size() - WideBwd<9>::nb) * eb + 4 * (size_t)WideBwd<9>::nb;
     if (e == hipSuccess) e = hipMalloc(&ctx->wide_bidx, sizeof(int) * bidx.size());
     if (e == hipSuccess) e = hipMalloc(&ctx->wide_bpacked, bbytes);
     if (e == hipSuccess)
@@ -782,10 +787,11 @@ lbm_status lbm_shift(lbm_ctx* ctx, const float* src, float* dst, int32_t directi
   LBM_GUARD_END
 }
 
-lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
-                             const float* lam_n1, float* lam_n, float* dtheta, void* ws,
-                             size_t ws_bytes, hipStream_t stream) {
-  LBM_GUARD_BEGIN
+// lbm_step_backward; pack false: the context's packed adjoint weights are
+// those of this theta already (an earlier step of the same sequence).
+static lbm_status step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
+                                const float* lam_n1, float* lam_n, float* dtheta, void* ws,
+                                size_t ws_bytes, hipStream_t stream, bool pack) {
   lbm_status st = check_ctx(ctx);
   if (st != LBM_OK) return st;
   if (!A_n || !lam_n1 || !lam_n) return fail(LBM_ERR_INVALID, "null array");
@@ -804,7 +810,7 @@ lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
     hipError_t e = wide_bwd_launch(c.lattice == LBM_D3Q19, prec_of(c.mlp_prec), stream, A_n, theta,
                                    lam_n1, lam_n, dtheta, ws, ctx->wide_bidx, ctx->wide_bpacked,
                                    grid_of(c), force_of(ctx), (float)c.rho0, (float)(1.0 / c.tau),
-                                   (float)(c.out_scale / c.tau));
+                                   (float)(c.out_scale / c.tau), pack);
     if (e != hipSuccess)
       return fail(LBM_ERR_HIP, std::string("wide-network adjoint: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -812,6 +818,13 @@ lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
   if (ctx->cfg.lattice == LBM_D2Q9)
     return run_backward<D2Q9>(ctx, A_n, theta, lam_n1, lam_n, dtheta, ws, stream);
   return run_backward<D3Q19>(ctx, A_n, theta, lam_n1, lam_n, dtheta, ws, stream);
+}
+
+lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
+                             const float* lam_n1, float* lam_n, float* dtheta, void* ws,
+                             size_t ws_bytes, hipStream_t stream) {
+  LBM_GUARD_BEGIN
+  return step_backward(ctx, A_n, theta, lam_n1, lam_n, dtheta, ws, ws_bytes, stream, true);
   LBM_GUARD_END
 }
 
@@ -875,7 +888,7 @@ lbm_status lbm_step_backward_seq(lbm_ctx* ctx, const float* const* A, int32_t ns
                ? run_backward<D2Q9>(ctx, A[m], theta, in, out, dtheta, ws, stream, accum, reduce)
                : run_backward<D3Q19>(ctx, A[m], theta, in, out, dtheta, ws, stream, accum, reduce);
     } else {
-      st = lbm_step_backward(ctx, A[m], theta, in, out, dtheta, ws, ws_bytes, stream);
+      st = step_backward(ctx, A[m], theta, in, out, dtheta, ws, ws_bytes, stream, m == nsteps - 1);
     }
     if (st != LBM_OK) return st;
     float* t = in;

@@ -1,0 +1,694 @@
+// wide_adj16.hpp -- adjoint of one step with the SI's network in bf16 / fp16
+// (the products and the data flow are those listed in wide_bwd.hpp; the
+// float32 network keeps the chain of products there).
+//
+// Two kernels and a reduction per step (D3Q19 bf16, one step: 32^3 262 -> 70 us,
+// 60 x 64 x 52 1,330 -> 385 us against a chain of fourteen products on 64 x 64
+// tiles, which wrote every activation twice and read it three times):
+//
+//   wide_adj_data_kernel     64 nodes per workgroup, from the gather to the
+//       scatter of lam^n: the hidden layers are recomputed and differentiated
+//       with the activations of the 64 nodes in LDS (two buffers of 38 KB,
+//       two workgroups per compute unit) and the weights streamed from the
+//       L2 into registers in the order of use.  What bounds it: matrix-core
+//       and VALU issue in about equal parts (608 matrix instructions and
+//       about 750 VALU instructions of epilogue per 16 nodes).  31.6 us at
+//       32^3, 193 us at 60 x 64 x 52 (0.52 PFLOP/s; its parts took 167 us
+//       at 32^3 as separate products).
+//   wide_adj_weight_kernel   the weight gradients, contractions over the
+//       nodes, from the activations the first kernel leaves in memory once
+//       (3.1 KB per node).  Bound by that read: 29 us at 32^3, 184 us at 60 x
+//       64 x 52 (3.5 TB/s; 72 and 375 us before).
+//   wide_adj_reduce_kernel   sums the node ranges' partial gradients: 9.4 us
+//       for 48 ranges (22.8 us at 32^3 and 57.4 us at 60 x 64 x 52 before,
+//       with 64 and 128 of them).
+//
+// Work split of the first kernel.  A wavefront computes five of a layer's
+// twenty 16-row tiles for all 64 nodes, so a weight fragment (read from the
+// L2 once per workgroup) feeds four matrix instructions and an activation
+// fragment (16 bytes per lane from LDS) five: at full matrix rate that is 64
+// B per clock of L2 reads and 51 of LDS reads per compute unit.  With whole
+// layers per wavefront (weights through LDS, activations in registers) the
+// LDS would have to deliver 128 B per clock.
+//
+// Fragment order.  The contraction of every product runs over chunks of 32
+// features, lane group g of 16 lanes holding features 8 g .. 8 g + 7 of the
+// chunk (an operand of one 16 x 16 x 32 matrix instruction).  The rows of
+// the two 16-row tiles of a pair are dealt so that lane group g's results
+// are features 8 g .. 8 g + 3 (first tile) and 8 g + 4 .. 8 g + 7 (second)
+// of the pair's 32: packed, they are the next product's operand.
+//
+// Node-tile record (kept for the second kernel): 50 blocks of 1 KB, one per
+// 16 nodes x 32 features, in the order X0, dY, H1 (10), H2 (10), H3 (4),
+// dZ3 (4), dZ2 (10), dZ1 (10).  Within a block, the 16 bytes of lane (g, i)
+// sit at slot 16 g + (i ^ 8 (g & 1)): the second kernel reads the block
+// transposed (node index as the contraction) with ds_read_b64_tr_b16, and the
+// exchange puts the sixteen 8-byte rows of each 16-lane group on different
+// bank pairs.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <vector>
+
+#include "kernels_bwd.hpp"
+#include "wide.hpp"
+#include "wide_bwd.hpp"
+
+namespace lbm {
+
+template <int Q_>
+struct WideAdj {
+  static constexpr int Q = Q_;
+  using W = WideBwd<Q>;
+  // layers of the first kernel in order: H1, H2, H3, dZ3, dZ2, dZ1, dX0;
+  // tiles per wavefront and contraction chunks of each
+  static constexpr int NL = 7;
+  static constexpr int TPW[NL] = {5, 5, 2, 2, 5, 5, 2};
+  static constexpr int KC[NL] = {1, 10, 10, 1, 4, 10, 10};
+  static constexpr int NSTEP = 46;  // chunks of all layers
+  static constexpr int layer_of(int s) {
+    int l = 0;
+    while (s >= KC[l]) s -= KC[l++];
+    return l;
+  }
+  static constexpr int first_step(int l) {
+    int s = 0;
+    for (int i = 0; i < l; ++i) s += KC[i];
+    return s;
+  }
+  // first fragment of step s in a wavefront's weight stream
+  static constexpr int frag_of(int s) {
+    int f = 0;
+    for (int i = 0; i < s; ++i) f += TPW[layer_of(i)];
+    return f;
+  }
+  static constexpr int NFW = 167;  // fragments of one wavefront's stream
+  static constexpr int NWAVE = 4;
+  static constexpr int nw = NWAVE * NFW * 512;  // packed weights (16-bit entries)
+  static constexpr int packed_bytes = 2 * nw + 4 * W::nb;
+  // A wavefront's tiles of a 20-tile layer: four that form two pairs, then
+  // one half of the pair it shares with its neighbour.
+  __host__ __device__ static constexpr int pair0(int w) { return (5 * w + 1) / 2; }
+  __host__ __device__ static constexpr int half_pair(int w) { return 2 + 5 * (w / 2); }
+  static constexpr int tile5(int w, int j) {
+    return j < 4 ? 2 * (pair0(w) + j / 2) + j % 2 : 2 * half_pair(w) + (w & 1);
+  }
+  // record blocks
+  static constexpr int RX0 = 0, RDY = 1, RH1 = 2, RH2 = 12, RH3 = 22, RZ3 = 26, RZ2 = 30, RZ1 = 40,
+                       NREC = 50;
+  // gradient tiles of a partial slab (256 floats each): dW2 (19 x 19), dW3 (7
+  // x 19), dW1 transposed (X0 x dZ1: 2 x 19), dW4 (2 x 7)
+  static constexpr int G2 = 0, G3 = G2 + 361, G1 = G3 + 133, G4 = G1 + 38, NG = G4 + 14;
+};
+
+// theta index of entry e of the packed weights (see WideAdj; -1 is zero),
+// then the bias vectors as in WideBwd (-2 is the constant 1).
+template <int Q>
+std::vector<int> wide_adj_index() {
+  using A = WideAdj<Q>;
+  using W = WideBwd<Q>;
+  std::vector<int> idx((size_t)A::nw + W::nb, -1);
+  auto value = [](int l, int o, int k) -> int {
+    switch (l) {
+      case 0: return o < W::N1 ? (k < Q ? W::pW1 + o * Q + k : (k == Q ? W::pb1 + o : -1)) : -1;
+      case 1: return o < W::N2 && k < W::N1 ? W::pW2 + o * W::N1 + k : -1;
+      case 2: return o < W::N3 && k < W::N2 ? W::pW3 + o * W::N2 + k : -1;
+      case 3: return o < W::N3 && k < Q ? W::pW4 + k * W::N3 + o : -1;
+      case 4: return o < W::N2 && k < W::N3 ? W::pW3 + k * W::N2 + o : -1;
+      case 5: return o < W::N1 && k < W::N2 ? W::pW2 + k * W::N1 + o : -1;
+      default: return o < Q && k < W::N1 ? W::pW1 + k * Q + o : -1;
+    }
+  };
+  for (int w = 0; w < A::NWAVE; ++w) {
+    int f = 0;
+    for (int l = 0; l < A::NL; ++l)
+      for (int c = 0; c < A::KC[l]; ++c)
+        for (int j = 0; j < A::TPW[l]; ++j, ++f)
+          for (int lane = 0; lane < 64; ++lane)
+            for (int e = 0; e < 8; ++e) {
+              const int i = lane & 15, k = 32 * c + 8 * (lane >> 4) + e;
+              const int t = A::TPW[l] == 5 ? A::tile5(w, j) : (l == A::NL - 1 ? j : 2 * w + j);
+              const int o = l == A::NL - 1 ? 16 * t + i
+                                           : 32 * (t / 2) + 8 * (i / 4) + 4 * (t % 2) + i % 4;
+              idx[((size_t)(w * A::NFW + f) * 64 + lane) * 8 + e] = value(l, o, k);
+            }
+  }
+  int* v = idx.data() + A::nw;
+  for (int j = 0; j < W::D1; ++j) v[W::fE1 + j] = j == W::ONE1 ? -2 : -1;
+  for (int j = 0; j < W::D2; ++j) v[W::fB2 + j] = j < W::N2 ? W::pb2 + j : (j == W::ONE2 ? -2 : -1);
+  for (int j = 0; j < W::D3; ++j) v[W::fB3 + j] = j < W::N3 ? W::pb3 + j : (j == W::ONE3 ? -2 : -1);
+  return idx;
+}
+
+template <int P>
+__device__ inline f4 mma32(u4 a, u4 b, f4 c) {
+  if constexpr (P == P_BF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a),
+                                                   __builtin_bit_cast(b8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a),
+                                                  __builtin_bit_cast(h8, b), c, 0, 0, 0);
+}
+
+// Byte offsets of one node per lane (any flat node index, so that no lane is
+// idle at the end of a row): the x, y and z parts of its own cell and its six
+// neighbours' in plane 0 of its field; population q's plane is q plane bytes
+// further on (a scalar offset).
+struct NodeOffsets {
+  int x, y, z;
+  unsigned xo[3], yo[3], zo[3];  // index 1 + c: coordinate minus c
+  __device__ inline void start(const Grid& G, int Q, unsigned node) {
+    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
+    unsigned r = node / nx;
+    x = (int)(node - r * nx);
+    unsigned s = r / ny;
+    y = (int)(r - s * ny);
+    const unsigned b = s / nz;
+    z = (int)(s - b * nz);
+#pragma unroll
+    for (int c = -1; c <= 1; ++c) {
+      xo[1 + c] = (unsigned)wrap_sub(x, c, G.nx) * 4u;
+      yo[1 + c] = (unsigned)wrap_sub(y, c, G.ny) * (nx * 4u);
+      zo[1 + c] = ((unsigned)wrap_sub(z, c, G.nz) + b * (unsigned)Q * nz) * (nx * ny * 4u);
+    }
+  }
+  // plane 0 offset of the cell population q is pulled from (and its adjoint
+  // pushed to)
+  template <class L>
+  __device__ inline int pull(int q) const {
+    return (int)(xo[1 + L::cx[q]] + yo[1 + L::cy[q]] + zo[1 + L::cz[q]]);
+  }
+  __device__ inline int at() const { return (int)(xo[1] + yo[1] + zo[1]); }
+};
+
+template <class L, int P>
+__global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
+    const float* __restrict__ A, const float* __restrict__ lam1, float* __restrict__ lam0,
+    const unsigned char* __restrict__ packed, unsigned char* __restrict__ rec, Grid G, Force Fc,
+    float rho0, float omega, float knn) {
+  constexpr int Q = L::Q;
+  using AJ = WideAdj<Q>;
+  using W = WideBwd<Q>;
+  // chunk c of an activation buffer: 4 node tiles of 1 KB; a tenth (H3-sized:
+  // fourth) chunk holds 16 features, 512 bytes per node tile
+  constexpr int BUF = 9 * 4096 + 2048;
+  __shared__ __attribute__((aligned(16))) unsigned char bufP[BUF];
+  __shared__ __attribute__((aligned(16))) unsigned char bufQ[BUF];
+  __shared__ __attribute__((aligned(16))) unsigned char bufE[4096];
+  constexpr int SDX = 36;  // row stride of the dX0 rows (floats) in bufQ
+  static_assert(64 * SDX * 4 <= BUF, "dX0 rows");
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, lg = lane >> 4, li = lane & 15;
+  const rsrc_t wsrc = make_rsrc(reinterpret_cast<const float*>(packed), (unsigned)AJ::packed_bytes);
+  const int wbase = wave * AJ::NFW * 1024, l16 = lane * 16;
+  const rsrc_t myrec = make_rsrc(
+      reinterpret_cast<const float*>(rec + (size_t)blockIdx.x * 4 * (AJ::NREC * 1024)),
+      4 * AJ::NREC * 1024);
+  const int slot16 = 16 * (16 * lg + (li ^ (8 * (lg & 1))));
+
+  // the weight stream: step s + 2's fragments are issued at step s
+  u4 ring[3][5];
+  auto issue = [&](auto sc) {
+    constexpr int s = decltype(sc)::value;
+    if constexpr (s < AJ::NSTEP) {
+      constexpr int n = AJ::TPW[AJ::layer_of(s)], f = AJ::frag_of(s);
+#pragma unroll
+      for (int j = 0; j < n; ++j)
+        ring[s % 3][j] = __builtin_bit_cast(
+            u4, __builtin_amdgcn_raw_buffer_load_b128(wsrc, l16, wbase + (f + j) * 1024, 0));
+    }
+  };
+  issue(std::integral_constant<int, 0>{});
+  issue(std::integral_constant<int, 1>{});
+
+  // wavefront 0, one node per lane: the gather, the network input, and
+  // (while the others start the hidden layers) the non-network adjoint
+  const unsigned total = (unsigned)G.plane * (unsigned)G.batch;
+  const unsigned node = blockIdx.x * 64u + lane;
+  const unsigned bytes = total * (unsigned)Q * 4u, plane4 = (unsigned)G.plane * 4u;
+  const rsrc_t rA = make_rsrc(A, bytes), rL1 = make_rsrc(lam1, bytes), rL0 = make_rsrc(lam0, bytes);
+  float lam[Q];
+  auto put_row = [&](unsigned char* buf, const float (&v)[32]) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      u4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = pack2<P>(v[8 * g + 2 * k], v[8 * g + 2 * k + 1]);
+      *reinterpret_cast<u4*>(buf + (lane >> 4) * 1024 + (16 * g + (lane & 15)) * 16) = o;
+    }
+  };
+  if (wave == 0) {
+    float g[Q], mu[Q], v[32];
+    const bool in = node < total;
+    NodeOffsets o;
+    if (in) {
+      o.start(G, Q, node);
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        g[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                             rA, o.pull<L>(q), (int)(q * plane4), 0));
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        mu[q] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rL1, o.at(), (int)(q * plane4), 0));
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = in ? (k < Q ? g[k] : (k == Q ? 1.f : 0.f)) : 0.f;
+    put_row(bufQ, v);
+    __syncthreads();
+    float nu[Q], F[3];
+    if (in) {
+      body_force(Fc, G, o.x, o.y, o.z, F);
+      collide_adjoint<L>(g, mu, rho0, omega, F, Fc.kind != 0, nu, lam);
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = (in && k < Q) ? knn * nu[k] : 0.f;
+    put_row(bufE, v);
+  } else {
+    __syncthreads();
+  }
+
+  // 16-byte operand of this lane: chunk c (of KCL) of node tile n
+  auto read = [&](const unsigned char* buf, int c, int n, bool half) -> u4 {
+    if (!half) return *reinterpret_cast<const u4*>(buf + c * 4096 + n * 1024 + l16);
+    u4 v = *reinterpret_cast<const u4*>(buf + c * 4096 + n * 512 + (lane & 31) * 16);
+    if (lg >= 2) v = u4{0u, 0u, 0u, 0u};
+    return v;
+  };
+
+  // LeakyReLU masks of the hidden layers: bit 15 - (4 n + r) of word j is set
+  // where the activation of row r of the wavefront's tile j at node tile n is
+  // > 0
+  unsigned m1[5] = {0, 0, 0, 0, 0}, m2[5] = {0, 0, 0, 0, 0}, m3[2] = {0, 0};
+  // an activation rounds to a positive operand value above half of the
+  // format's smallest positive number
+  constexpr float kTiny = P == P_BF16 ? 0x1p-134f : 0x1p-25f;
+
+  // One product of the chain: acc[j][n] over the chunks of layer l, then
+  // ep(acc, n) per node tile.  rd(c, n): operand of chunk c and node tile n.
+  auto layer = [&](auto lc, auto&& rd, auto&& ep) {
+    constexpr int l = decltype(lc)::value, T = AJ::TPW[l], KCL = AJ::KC[l],
+                  s0 = AJ::first_step(l);
+    f4 acc[T][4];
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) acc[j][n] = f4{0.f, 0.f, 0.f, 0.f};
+    u4 xb[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) xb[n] = rd(0, n);
+    static_for<KCL>([&](auto cc) {
+      constexpr int c = decltype(cc)::value, s = s0 + c;
+      issue(std::integral_constant<int, s + 2>{});
+      static_for<4>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[j][n] = mma32<P>(ring[s % 3][j], xb[n], acc[j][n]);
+        // the next chunk's operand, into the registers just consumed
+        if constexpr (c + 1 < KCL) xb[n] = rd(c + 1, n);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+    static_for<4>([&](auto nc) {
+      ep(acc, decltype(nc)::value);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
+  auto put_rec = [&](int blk, int n, u4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, myrec, slot16, (n * AJ::NREC + blk) * 1024, 0);
+  };
+  // Results as operands, to LDS where a later product reads them (buf) and
+  // to the record: a pair of tiles, or the half hh of a shared pair.  Only
+  // the second pair of wavefront 3 (`tail`) is a layer's last chunk, which
+  // holds 16 features: half of the lanes, 512 bytes per node tile.
+  const int p0 = AJ::pair0(wave), ph = AJ::half_pair(wave), hh = wave & 1;
+  const int tail = wave == 3, tstride = tail ? 512 : 1024;
+  const bool tlive = !tail || lane < 32;
+  auto put_pair = [&](unsigned char* buf, int rblk, int p, int n, u2 lo, u2 hi) {
+    const u4 o = {lo[0], lo[1], hi[0], hi[1]};
+    put_rec(rblk + p, n, o);
+    *reinterpret_cast<u4*>(buf + p * 4096 + n * 1024 + l16) = o;
+  };
+  auto put_tail = [&](unsigned char* buf, int rblk, int p, int n, u2 lo, u2 hi) {
+    const u4 o = {lo[0], lo[1], hi[0], hi[1]};
+    put_rec(rblk + p, n, o);
+    if (tlive) *reinterpret_cast<u4*>(buf + p * 4096 + n * tstride + l16) = o;
+  };
+  // node tile n of a 20-tile layer
+  auto put5 = [&](unsigned char* buf, int rblk, int n, const u2 (&f)[5]) {
+    put_pair(buf, rblk, p0, n, f[0], f[1]);
+    put_tail(buf, rblk, p0 + 1, n, f[2], f[3]);
+    __builtin_amdgcn_raw_buffer_store_b64(f[4], myrec, slot16 + 8 * hh,
+                                          (n * AJ::NREC + rblk + ph) * 1024, 0);
+    *reinterpret_cast<u2*>(buf + ph * 4096 + n * 1024 + l16 + 8 * hh) = f[4];
+  };
+  // first feature of this lane's rows of tile j
+  auto feat5 = [&](int j) {
+    return j < 4 ? 32 * (p0 + j / 2) + 8 * lg + 4 * (j % 2) : 32 * ph + 8 * lg + 4 * hh;
+  };
+  const float* vec = reinterpret_cast<const float*>(packed + 2 * (size_t)AJ::nw);
+  // h = leaky(acc + bias) in the operand type; its four mask bits are
+  // shifted into m, the last row in bit 0 (h rounds to a positive value where
+  // kTiny - h is negative)
+  auto activate = [&](f4 a, f4 bias, unsigned& m) -> u2 {
+    f4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float t = a[r] + bias[r], st = kLeakySlope * t;
+      // max(t, slope t), without the quieting of NaNs that fmaxf adds
+      asm("v_max_f32 %0, %1, %2" : "=v"(v[r]) : "v"(t), "v"(st));
+      m = __builtin_amdgcn_alignbit(m, __builtin_bit_cast(unsigned, kTiny - v[r]), 31);
+    }
+    asm("" : "+v"(m));  // (the compiler would keep the sixteen values instead)
+    return to_frag<P>(v);
+  };
+  // acc times the mask's factor, 1 or the slope
+  auto masked = [&](f4 a, unsigned m, int n) -> u2 {
+    constexpr unsigned one = 0x3F800000u, slope = __builtin_bit_cast(unsigned, kLeakySlope);
+    f4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const unsigned on = (unsigned)__builtin_amdgcn_sbfe((int)m, 15 - (4 * n + r), 1);
+      v[r] = a[r] * __builtin_bit_cast(float, (on & one) | (~on & slope));
+    }
+    return to_frag<P>(v);
+  };
+  auto bias_of = [&](int base, int feat, int dim) {
+    // (features past the padded width have no entry and stay zero)
+    return feat < dim ? *reinterpret_cast<const f4*>(vec + base + feat) : f4{0.f, 0.f, 0.f, 0.f};
+  };
+
+  // the bias rows of the wavefront's tiles
+  f4 bv[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) bv[j] = bias_of(W::fE1, feat5(j), W::D1);
+  // H1 = leaky(X0 W1^T) (b1 in column Q, the constant column from the bias vector)
+  layer(
+      std::integral_constant<int, 0>{},
+      [&](int, int n) {
+        const u4 v = read(bufQ, 0, n, false);
+        if (n == wave) put_rec(AJ::RX0, n, v);
+        return v;
+      },
+      [&](const f4 (&acc)[5][4], int n) {
+        u2 f[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) f[j] = activate(acc[j][n], bv[j], m1[j]);
+        put5(bufP, AJ::RH1, n, f);
+      });
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 5; ++j) bv[j] = bias_of(W::fB2, feat5(j), W::D2);
+  // H2 = leaky(H1 W2^T + b2)
+  layer(
+      std::integral_constant<int, 1>{}, [&](int c, int n) { return read(bufP, c, n, c == 9); },
+      [&](const f4 (&acc)[5][4], int n) {
+        u2 f[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) f[j] = activate(acc[j][n], bv[j], m2[j]);
+        put5(bufQ, AJ::RH2, n, f);
+      });
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) bv[j] = bias_of(W::fB3, 32 * wave + 8 * lg + 4 * j, W::D3);
+  // H3 = leaky(H2 W3^T + b3): only its mask and the record are needed
+  layer(
+      std::integral_constant<int, 2>{}, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
+      [&](const f4 (&acc)[2][4], int n) {
+        u2 f[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) f[j] = activate(acc[j][n], bv[j], m3[j]);
+        put_rec(AJ::RH3 + wave, n, u4{f[0][0], f[0][1], f[1][0], f[1][1]});
+      });
+  // dZ3 = (dY W4) . leaky'(H3)
+  layer(
+      std::integral_constant<int, 3>{},
+      [&](int, int n) {
+        const u4 v = read(bufE, 0, n, false);
+        if (n == wave) put_rec(AJ::RDY, n, v);
+        return v;
+      },
+      [&](const f4 (&acc)[2][4], int n) {
+        put_tail(bufP, AJ::RZ3, wave, n, masked(acc[0][n], m3[0], n), masked(acc[1][n], m3[1], n));
+      });
+  __syncthreads();
+  // dZ2 = (dZ3 W3) . leaky'(H2)
+  layer(
+      std::integral_constant<int, 4>{}, [&](int c, int n) { return read(bufP, c, n, c == 3); },
+      [&](const f4 (&acc)[5][4], int n) {
+        u2 f[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) f[j] = masked(acc[j][n], m2[j], n);
+        put5(bufQ, AJ::RZ2, n, f);
+      });
+  __syncthreads();
+  // dZ1 = (dZ2 W2) . leaky'(H1)
+  layer(
+      std::integral_constant<int, 5>{}, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
+      [&](const f4 (&acc)[5][4], int n) {
+        u2 f[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) f[j] = masked(acc[j][n], m1[j], n);
+        put5(bufP, AJ::RZ1, n, f);
+      });
+  __syncthreads();
+  // dX0 = dZ1 W1: wavefront w takes node tile w, rows of the inputs
+  {
+    constexpr int s0 = AJ::first_step(6);
+    f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    static_for<10>([&](auto cc) {
+      constexpr int c = decltype(cc)::value, s = s0 + c;
+      issue(std::integral_constant<int, s + 2>{});
+      const u4 xv = read(bufP, c, wave, c == 9);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j] = mma32<P>(ring[s % 3][j], xv, acc[j]);
+    });
+    float* DX = reinterpret_cast<float*>(bufQ);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      *reinterpret_cast<f4*>(DX + (16 * wave + li) * SDX + 16 * j + 4 * lg) = acc[j];
+  }
+  __syncthreads();
+  // lam^n_q(x - c_q): the non-network adjoint plus the input gradient
+  if (wave == 0 && node < total) {
+    const float* DX = reinterpret_cast<const float*>(bufQ) + lane * SDX;
+    unsigned nd = node;
+    asm("" : "+v"(nd));  // (formed again rather than kept through the layers)
+    NodeOffsets e;
+    e.start(G, Q, nd);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, lam[q] + DX[q]), rL0,
+                                            e.pull<L>(q), (int)(q * plane4), 0);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients.  Ten sets of 16 x 16 gradient tiles, each a product of
+// some record blocks over the nodes: dW2 in six (rows 0-7, 8-13, 14-18 x
+// columns 0-9, 10-18), dW3 in two, dW1 and dW4.  A workgroup takes one set
+// over one range of nodes and walks it 32 nodes at a time; the set's blocks
+// of the 32 nodes come into LDS by direct loads, two steps ahead in three
+// buffers.  The ten sets of a node range run on one XCD (workgroups go round
+// the eight XCDs), so that the blocks two or three sets share come from its
+// L2.
+// ---------------------------------------------------------------------------
+struct WideSet {
+  int nrow, row0;  // row blocks: number, first record block
+  int ncol, col0;  // column blocks
+  int gr0, gc0;    // first gradient tile row and column
+  int rows, cols;  // tile rows and columns of the whole matrix
+  int slab;        // first slab tile of the matrix
+};
+constexpr int kWideSets = 10;
+
+template <int Q>
+__device__ constexpr WideSet wide_set(int s) {
+  using A = WideAdj<Q>;
+  switch (s) {
+    case 0: return {4, A::RZ2, 5, A::RH1, 0, 0, 19, 19, A::G2};
+    case 1: return {4, A::RZ2, 5, A::RH1 + 5, 0, 10, 19, 19, A::G2};
+    case 2: return {3, A::RZ2 + 4, 5, A::RH1, 8, 0, 19, 19, A::G2};
+    case 3: return {3, A::RZ2 + 4, 5, A::RH1 + 5, 8, 10, 19, 19, A::G2};
+    case 4: return {3, A::RZ2 + 7, 5, A::RH1, 14, 0, 19, 19, A::G2};
+    case 5: return {3, A::RZ2 + 7, 5, A::RH1 + 5, 14, 10, 19, 19, A::G2};
+    case 6: return {4, A::RZ3, 5, A::RH2, 0, 0, 7, 19, A::G3};
+    case 7: return {4, A::RZ3, 5, A::RH2 + 5, 0, 10, 7, 19, A::G3};
+    case 8: return {1, A::RX0, 10, A::RZ1, 0, 0, 2, 19, A::G1};
+    default: return {1, A::RDY, 4, A::RH3, 0, 0, 2, 7, A::G4};
+  }
+}
+
+// vmcnt(n), other counters unconstrained
+template <int n>
+__device__ inline void wait_loads() {
+  static_assert(n < 16, "vmcnt field");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | n);
+}
+
+constexpr int kWideStageBytes = 11 * 2048;
+
+template <int Q, int P, int S>
+__device__ __forceinline__ void wide_adj_weights(const unsigned char* __restrict__ rec,
+                                                 float* __restrict__ slab, int step0, int steps,
+                                                 unsigned char* st0, unsigned char* st1,
+                                                 unsigned char* st2) {
+  using AJ = WideAdj<Q>;
+  constexpr WideSet D = wide_set<Q>(S);
+  constexpr int NB = D.nrow + D.ncol, NLD = (2 * NB + 3) / 4;
+  // wavefronts: 2 x 2 over (rows, columns); 1 x 4 over the columns where
+  // there is one row block
+  constexpr bool TALL = D.nrow > 1;
+  constexpr int NR = TALL ? D.nrow : 2, NC = TALL ? D.ncol : (2 * D.ncol + 3) / 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, lg = lane >> 4, li = lane & 15;
+  const int ur = TALL ? (wave >> 1) * NR : 0, uc = (TALL ? (wave & 1) : wave) * NC;
+  f4 acc[NR][NC];
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+
+  // staged block k: 0..nrow-1 the rows, then the columns, each for the two
+  // node tiles of the step (1 KB per block and node tile); every wavefront
+  // issues NLD loads, the last one again where there are fewer
+  const unsigned char* src = rec + (size_t)step0 * 2 * (AJ::NREC * 1024);
+  auto issue = [&](int i, unsigned char* st) {
+    if (i >= steps) return;
+    const rsrc_t r = make_rsrc(reinterpret_cast<const float*>(src + (size_t)i * 2 * (AJ::NREC * 1024)),
+                               2 * AJ::NREC * 1024);
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) {
+      int k = wave + 4 * q;
+      if (k >= 2 * NB) k = 2 * NB - 1;
+      const int blk = k >> 1, nt = k & 1;
+      const int rb = blk < D.nrow ? D.row0 + blk : D.col0 + blk - D.nrow;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          r, (__attribute__((address_space(3))) void*)(st + k * 1024), 16, lane * 16,
+          (nt * AJ::NREC + rb) * 1024, 0, 0);
+    }
+  };
+  // transposed read: this lane addresses the 8-byte row of node 4 (lane / 16)
+  // + (lane % 16) / 4, features 4 a .. 4 a + 3 (a = lane % 4) of the unit
+  const int a = lane & 3, nd = 4 * lg + (li >> 2);
+  const int tr = 16 * (16 * (a >> 1) + (nd ^ (8 * (a >> 1)))) + 8 * (a & 1);
+  auto unit = [&](const unsigned char* st, int blk, int u) -> u4 {
+    const unsigned char* p = st + blk * 2048 + u * 512 + tr;
+    const u2 v0 = read_tr<P>(p), v1 = read_tr<P>(p + 1024);
+    return u4{v0[0], v0[1], v1[0], v1[1]};
+  };
+  auto compute = [&](const unsigned char* st) {
+    u4 ra[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) ra[i] = unit(st, (ur + i) >> 1, (ur + i) & 1);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      int u = uc + j;
+      if (u >= 2 * D.ncol) u = 2 * D.ncol - 1;
+      const u4 cb = unit(st, D.nrow + (u >> 1), u & 1);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) acc[i][j] = mma32<P>(ra[i], cb, acc[i][j]);
+    }
+  };
+  auto turn = [&](int i, const unsigned char* cur, unsigned char* fill) {
+    if (i + 1 < steps)
+      wait_loads<NLD>();
+    else
+      wait_loads<0>();
+    __syncthreads();
+    issue(i + 2, fill);
+    compute(cur);
+  };
+  issue(0, st0);
+  issue(1, st1);
+  for (int i = 0; i < steps; i += 3) {
+    turn(i, st0, st2);
+    if (i + 1 < steps) turn(i + 1, st1, st0);
+    if (i + 2 < steps) turn(i + 2, st2, st1);
+  }
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int r = D.gr0 + ur + i, c = D.gc0 + uc + j;
+      if (r < D.rows && c < D.cols && uc + j < 2 * D.ncol)
+        *reinterpret_cast<f4*>(slab + ((size_t)(D.slab + r * D.cols + c) * 64 + lane) * 4) = acc[i][j];
+    }
+}
+
+// grid: sets x splits; split k covers steps [k per, k per + per) of 32 nodes
+// and writes slab k.
+template <int Q, int P>
+__global__ __launch_bounds__(256, 2) void wide_adj_weight_kernel(
+    const unsigned char* __restrict__ rec, float* __restrict__ part, int nsteps, int per, int nsplit) {
+  __shared__ __attribute__((aligned(16))) unsigned char st0[kWideStageBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char st1[kWideStageBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char st2[kWideStageBytes];
+  int set, split;
+  if (nsplit % 8 == 0) {
+    const int i = blockIdx.x / 8;
+    split = blockIdx.x % 8 + 8 * (i / kWideSets);
+    set = i % kWideSets;
+  } else {
+    split = blockIdx.x / kWideSets;
+    set = blockIdx.x % kWideSets;
+  }
+  const int step0 = split * per, steps = min(per, nsteps - step0);
+  float* slab = part + (size_t)split * (WideAdj<Q>::NG * 256);
+  switch (set) {
+    case 0: wide_adj_weights<Q, P, 0>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 1: wide_adj_weights<Q, P, 1>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 2: wide_adj_weights<Q, P, 2>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 3: wide_adj_weights<Q, P, 3>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 4: wide_adj_weights<Q, P, 4>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 5: wide_adj_weights<Q, P, 5>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 6: wide_adj_weights<Q, P, 6>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 7: wide_adj_weights<Q, P, 7>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 8: wide_adj_weights<Q, P, 8>(rec, slab, step0, steps, st0, st1, st2); break;
+    default: wide_adj_weights<Q, P, 9>(rec, slab, step0, steps, st0, st1, st2); break;
+  }
+}
+
+// dtheta += the sum over the slabs, in a fixed order.  One workgroup per
+// gradient tile: wavefront w sums slabs w, w + 4, ..., the four sums are
+// added in wave order.
+template <int Q>
+__global__ __launch_bounds__(256) void wide_adj_reduce_kernel(const float* __restrict__ part,
+                                                              int nsplit,
+                                                              float* __restrict__ dtheta) {
+  using AJ = WideAdj<Q>;
+  using W = WideBwd<Q>;
+  __shared__ f4 red[4][64];
+  const int t = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  f4 s = {0.f, 0.f, 0.f, 0.f};
+  for (int k = w; k < nsplit; k += 4)
+    s += *reinterpret_cast<const f4*>(part + ((size_t)k * AJ::NG + t) * 256 + lane * 4);
+  red[w][lane] = s;
+  __syncthreads();
+  if (w != 0) return;
+  s = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+  const int r0 = 4 * (lane >> 4), c0 = lane & 15;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    int p = -1;
+    if (t < AJ::G3) {
+      const int i = 16 * (t / 19) + r0 + r, j = 16 * (t % 19) + c0;
+      if (i < W::N2) p = j < W::N1 ? W::pW2 + i * W::N1 + j : (j == W::ONE1 ? W::pb2 + i : -1);
+    } else if (t < AJ::G1) {
+      const int i = 16 * ((t - AJ::G3) / 19) + r0 + r, j = 16 * ((t - AJ::G3) % 19) + c0;
+      if (i < W::N3) p = j < W::N2 ? W::pW3 + i * W::N2 + j : (j == W::ONE2 ? W::pb3 + i : -1);
+    } else if (t < AJ::G4) {  // rows: input features, columns: layer-1 units
+      const int i = 16 * ((t - AJ::G1) / 19) + r0 + r, j = 16 * ((t - AJ::G1) % 19) + c0;
+      if (j < W::N1) p = i < Q ? W::pW1 + j * Q + i : (i == Q ? W::pb1 + j : -1);
+    } else {
+      const int i = 16 * ((t - AJ::G4) / 7) + r0 + r, j = 16 * ((t - AJ::G4) % 7) + c0;
+      if (i < Q) p = j < W::N3 ? W::pW4 + i * W::N3 + j : (j == W::ONE3 ? W::pb4 + i : -1);
+    }
+    if (p >= 0) dtheta[p] += s[r];
+  }
+}
+
+}  // namespace lbm

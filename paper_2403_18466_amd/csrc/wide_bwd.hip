@@ -1,6 +1,7 @@
 // wide_bwd.hip -- host sequence of the wide network's adjoint (wide_bwd.hpp).
 #include <hip/hip_runtime.h>
 
+#include "wide_adj16.hpp"
 #include "wide_bwd.hpp"
 
 namespace lbm {
@@ -57,10 +58,7 @@ WsLayout ws_layout(long long nodes, size_t es) {
 template <int P, int EPI>
 hipError_t gemm(hipStream_t s, const GemmArgs& a, long long M, int N, int splits) {
   dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)splits);
-  if constexpr (P == P_F32)
-    hipLaunchKernelGGL((gemm_nt_kernel<P, EPI>), grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_nt16_kernel<P, EPI>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_nt_kernel<P, EPI>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -86,10 +84,53 @@ GemmArgs args(const void* A, long long lda, const void* B, long long ldb, int M,
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
+// The 16-bit networks (wide_adj16.hpp): node-tile records at the start of the
+// workspace, then one gradient slab per node range.  The workspace keeps the
+// size of the product chain's layout, which holds every activation twice:
+// the records (3200 bytes per node against 6144) leave room for at least as
+// many slabs.
+template <class L, int P>
+hipError_t run16(hipStream_t s, const float* A, const float* theta, const float* lam1, float* lam0,
+                 float* dtheta, void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
+                 float rho0, float omega, float knn, bool pack) {
+  using W = WideBwd<L::Q>;
+  using AJ = WideAdj<L::Q>;
+  const long long nodes = (long long)G.plane * G.batch;
+  const WsLayout l = ws_layout<L::Q>(nodes, 2);
+  const size_t rec_bytes = (size_t)l.Np / 16 * (AJ::NREC * 1024), slab = (size_t)AJ::NG * 1024;
+  unsigned char* rec = static_cast<unsigned char*>(ws);
+  float* part = reinterpret_cast<float*>(rec + rec_bytes);
+  // Node ranges of the weight gradients: 48 x 10 workgroups fill the chip (two
+  // per compute unit) on the large grids; at least eight steps of 32 nodes
+  // per range on the small ones, whose cost is the slabs' write and sum.
+  const int nsteps = (int)(l.Np / 32);
+  long long room = (long long)((l.total - rec_bytes) / slab), ns = (nsteps + 7) / 8;
+  if (ns > 48) ns = 48;
+  if (ns > room) ns = room;
+  if (ns > 8) ns -= ns % 8;
+  const int per = (int)((nsteps + ns - 1) / ns);
+  const int nsplit = (nsteps + per - 1) / per;
+
+  if (pack) {
+    hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((AJ::nw + W::nb + 255) / 256), dim3(256), 0, s,
+                       theta, idx, packed, AJ::nw, W::nb);
+    WB_CHECK(hipGetLastError());
+  }
+  hipLaunchKernelGGL((wide_adj_data_kernel<L, P>), dim3((unsigned)(l.Np / 64)), dim3(256), 0, s, A,
+                     lam1, lam0, packed, rec, G, Fc, rho0, omega, knn);
+  WB_CHECK(hipGetLastError());
+  hipLaunchKernelGGL((wide_adj_weight_kernel<L::Q, P>), dim3((unsigned)(kWideSets * nsplit)),
+                     dim3(256), 0, s, rec, part, nsteps, per, nsplit);
+  WB_CHECK(hipGetLastError());
+  hipLaunchKernelGGL(wide_adj_reduce_kernel<L::Q>, dim3(AJ::NG), dim3(256), 0, s, part, nsplit,
+                     dtheta);
+  return hipGetLastError();
+}
+
 template <class L, int P>
 hipError_t run(hipStream_t s, const float* A, const float* theta, const float* lam1, float* lam0,
                float* dtheta, void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
-               float rho0, float omega, float knn) {
+               float rho0, float omega, float knn, bool pack) {
   using W = WideBwd<L::Q>;
   using T = typename OpT<P>::T;
   const long long nodes = (long long)G.plane * G.batch;
@@ -100,9 +141,11 @@ hipError_t run(hipStream_t s, const float* A, const float* theta, const float* l
   const float* vec = reinterpret_cast<const float*>(packed + (size_t)W::nw * sizeof(T));
   const unsigned nb_nodes = (unsigned)((l.Np + 255) / 256);
 
-  hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((W::nw + W::nb + 255) / 256), dim3(256), 0, s,
-                     theta, idx, packed, W::nw, W::nb);
-  WB_CHECK(hipGetLastError());
+  if (pack) {
+    hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((W::nw + W::nb + 255) / 256), dim3(256), 0, s,
+                       theta, idx, packed, W::nw, W::nb);
+    WB_CHECK(hipGetLastError());
+  }
   hipLaunchKernelGGL((wide_prep_kernel<L, P>), dim3(nb_nodes), dim3(256), 0, s, A, G, l.Np,
                      at(l.X0), at(l.X0t));
   WB_CHECK(hipGetLastError());
@@ -185,11 +228,11 @@ hipError_t run(hipStream_t s, const float* A, const float* theta, const float* l
 template <class L>
 hipError_t run_prec(int prec, hipStream_t s, const float* A, const float* theta, const float* lam1,
                     float* lam0, float* dtheta, void* ws, const int* idx, unsigned char* packed,
-                    Grid G, Force Fc, float rho0, float omega, float knn) {
+                    Grid G, Force Fc, float rho0, float omega, float knn, bool pack) {
   switch (prec) {
-    case P_F32: return run<L, P_F32>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn);
-    case P_BF16: return run<L, P_BF16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn);
-    default: return run<L, P_F16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn);
+    case P_F32: return run<L, P_F32>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
+    case P_BF16: return run16<L, P_BF16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
+    default: return run16<L, P_F16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
   }
 }
 
@@ -203,10 +246,10 @@ size_t wide_bwd_workspace_bytes(bool d3q19, int prec, long long nodes) {
 hipError_t wide_bwd_launch(bool d3q19, int prec, hipStream_t s, const float* A,
                            const float* theta, const float* lam1, float* lam0, float* dtheta,
                            void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
-                           float rho0, float omega, float knn) {
+                           float rho0, float omega, float knn, bool pack) {
   if (d3q19)
-    return run_prec<D3Q19>(prec, s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn);
-  return run_prec<D2Q9>(prec, s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn);
+    return run_prec<D3Q19>(prec, s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
+  return run_prec<D2Q9>(prec, s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
 }
 
 }  // namespace lbm

@@ -5,7 +5,9 @@
 // LeakyReLU derivative and the weight gradients) and the weight gradients
 // are contractions over all nodes.  Training runs on coarse grids (32^3 -
 // 64^3), so the adjoint is organised as dense products over the node
-// dimension with the activations kept in a caller workspace:
+// dimension with the activations kept in a caller workspace (here for the
+// float32 network; the 16-bit ones run the same data flow in the two fused
+// kernels of wide_adj16.hpp):
 //
 //   prep      X0 = [g, 1, 0...]                       (node kernel, gather)
 //   forward   H1 = leaky(X0 W1^T), H2 = leaky(H1 W2^T + b2), H3 = leaky(H2 W3^T + b3)
@@ -303,132 +305,6 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
   gemm_epilogue<P, EPI>(a, acc, i0 + wi, j0 + wj, lg, li);
 }
 
-// The same product for 16-bit operands, 64 x 64 tiles of four wavefronts
-// (32 x 32 each, 2 x 2 MFMA tiles), K steps of 32:
-//  * every thread loads 8 consecutive k of one row of A and of B per step
-//    (16-byte loads; M, N and K are multiples of 8 here, so a chunk is
-//    either wholly inside or wholly outside the operand);
-//  * the next step's chunks are in registers while the current step's
-//    MFMAs run, then go to the other of two LDS buffers (one barrier per
-//    step);
-//  * a lane's operand of one 16 x 16 x 32 MFMA is one 16-byte LDS read: row
-//    li of the tile, k = 8 lg .. 8 lg + 7, for A and for B alike, so the
-//    contraction pairs the same k on both sides.
-template <int P, int EPI>
-__global__ __launch_bounds__(256) void gemm_nt16_kernel(GemmArgs a) {
-  static_assert(P != P_F32, "16-bit operands");
-  using T = typename OpT<P>::T;
-  constexpr int SK = 32 + 8;  // LDS row stride (elements): 80 bytes
-  __shared__ __attribute__((aligned(16))) T As[2][64 * SK];
-  __shared__ __attribute__((aligned(16))) T Bs[2][64 * SK];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lg = lane >> 4, li = lane & 15;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const long long k_begin = (long long)blockIdx.z * a.kc;
-  long long k_end = k_begin + a.kc;
-  if (k_end > a.K) k_end = a.K;
-  const T* A = static_cast<const T*>(a.A);
-  const T* B = static_cast<const T*>(a.B);
-  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
-  // staging: thread -> row tid / 4 of each tile, k (tid % 4) * 8 .. + 7
-  const int sr = tid >> 2, sk = (tid & 3) * 8;
-  const bool rowA = i0 + sr < a.M, rowB = j0 + sr < a.N;
-  const T* pa = A + (long long)(rowA ? i0 + sr : 0) * a.lda + sk;
-  const T* pb = B + (long long)(rowB ? j0 + sr : 0) * a.ldb + sk;
-  auto fetch = [&](long long k0, u4& va, u4& vb) {
-    const bool in = k0 + sk < k_end;
-    va = (rowA && in) ? *reinterpret_cast<const u4*>(pa + k0) : u4{0u, 0u, 0u, 0u};
-    vb = (rowB && in) ? *reinterpret_cast<const u4*>(pb + k0) : u4{0u, 0u, 0u, 0u};
-  };
-  f4 acc[2][2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) acc[s][t] = f4{0.f, 0.f, 0.f, 0.f};
-  u4 va, vb;
-  fetch(k_begin, va, vb);
-  *reinterpret_cast<u4*>(&As[0][sr * SK + sk]) = va;
-  *reinterpret_cast<u4*>(&Bs[0][sr * SK + sk]) = vb;
-  __syncthreads();
-  int buf = 0;
-  for (long long k0 = k_begin; k0 < k_end; k0 += 32) {
-    const bool more = k0 + 32 < k_end;
-    if (more) fetch(k0 + 32, va, vb);
-    u4 af[2], bf[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      af[s] = *reinterpret_cast<const u4*>(&As[buf][(wi + 16 * s + li) * SK + 8 * lg]);
-      bf[s] = *reinterpret_cast<const u4*>(&Bs[buf][(wj + 16 * s + li) * SK + 8 * lg]);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        if constexpr (P == P_BF16)
-          acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(b8, af[s]), __builtin_bit_cast(b8, bf[t]), acc[s][t], 0, 0, 0);
-        else
-          acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-              __builtin_bit_cast(h8, af[s]), __builtin_bit_cast(h8, bf[t]), acc[s][t], 0, 0, 0);
-      }
-    if (more) {
-      *reinterpret_cast<u4*>(&As[buf ^ 1][sr * SK + sk]) = va;
-      *reinterpret_cast<u4*>(&Bs[buf ^ 1][sr * SK + sk]) = vb;
-    }
-    __syncthreads();
-    buf ^= 1;
-  }
-  if constexpr (EPI == EPI_LEAKY || EPI == EPI_MASK) {
-    // The activations of the 64 x 64 tile go through LDS (the A buffers are
-    // free after the last barrier), so that both C and its transpose Ct are
-    // written as 16-byte row chunks.
-    constexpr int SO = 64 + 8;  // row stride of the output tile (elements)
-    static_assert(64 * SO <= 2 * 64 * SK, "output tile fits in the A buffers");
-    T* Ts = &As[0][0];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int jl = wj + 16 * t + li, j = j0 + jl;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int il = wi + 16 * s + 4 * lg + r, i = i0 + il;
-          float v = acc[s][t][r];
-          if constexpr (EPI == EPI_LEAKY) {
-            v += j < a.N ? a.bias[j] : 0.f;
-            v = v > 0.f ? v : kLeakySlope * v;
-          } else {
-            const float m = (i < a.M && j < a.N)
-                                ? (float)static_cast<const T*>(a.mask)[(long long)i * a.ldc + j]
-                                : 0.f;
-            v = m > 0.f ? v : kLeakySlope * v;
-          }
-          Ts[il * SO + jl] = to_op<P>(v);
-        }
-      }
-    __syncthreads();
-    T* C = static_cast<T*>(a.C);
-    T* Ct = static_cast<T*>(a.Ct);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c = tid + 256 * h, row = c >> 3, ch = (c & 7) * 8;
-      // C: row i0 + row, columns j0 + ch .. + 7
-      if (i0 + row < a.M && j0 + ch < a.N)
-        *reinterpret_cast<u4*>(C + (long long)(i0 + row) * a.ldc + j0 + ch) =
-            *reinterpret_cast<const u4*>(Ts + row * SO + ch);
-      // Ct: row j0 + row of the transpose, columns i0 + ch .. + 7
-      if (Ct && j0 + row < a.N && i0 + ch < a.M) {
-        T v8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v8[e] = Ts[(ch + e) * SO + row];
-        *reinterpret_cast<u4*>(Ct + (long long)(j0 + row) * a.ldct + i0 + ch) =
-            __builtin_bit_cast(u4, v8);
-      }
-    }
-  } else {
-    gemm_epilogue<P, EPI>(a, acc, i0 + wi, j0 + wj, lg, li);
-  }
-}
-
 // dtheta[p] += sum over the nsplit slabs (fixed order) of the padded weight
 // gradient entry that parameter p maps to.
 template <int Q>
@@ -467,10 +343,12 @@ __global__ __launch_bounds__(256) void wide_grad_reduce_kernel(const float* __re
 // Launch of the whole adjoint (defined in wide_bwd.hip).  ws: device
 // workspace of wide_bwd_workspace_bytes(); packed: the fragment buffer the
 // context owns, filled from theta by the call.
+// (pack false: packed still holds this theta, from an earlier call on the
+// same stream).
 size_t wide_bwd_workspace_bytes(bool d3q19, int prec, long long nodes);
 hipError_t wide_bwd_launch(bool d3q19, int prec, hipStream_t s, const float* A,
                            const float* theta, const float* lam1, float* lam0, float* dtheta,
                            void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
-                           float rho0, float omega, float knn);
+                           float rho0, float omega, float knn, bool pack);
 
 }  // namespace lbm

@@ -300,3 +300,73 @@ def test_wide_unrolled_gradient(lbm):
     assert abs(loss.item() - wl) <= 1e-5 * wl
     assert err < 1e-5
     L.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("lat,shape,batch,force", [
+    ("D2Q9", (1, 3, 5), 1, 0),      # less than one 16-node tile
+    ("D2Q9", (1, 8, 8), 1, 1),      # exactly one workgroup of 64 nodes
+    ("D3Q19", (5, 13, 1), 1, 0),    # one node more (65), a dimension of 1
+    ("D3Q19", (3, 7, 31), 2, 2),    # 1302 nodes: several node ranges, fewer than 8
+])
+def test_wide_adjoint_16bit_edges(lbm, lat, shape, batch, force, prec):
+    """The 16-bit adjoint where its node tiles, workgroups and node ranges
+    end, against the oracle's emulated-rounding adjoint.  The GPU also rounds
+    dY and dZ1-dZ3 to the operand format (relative 2^-9 / 2^-12 each): bars of
+    ten such roundings for dtheta, a tenth of that for lam, whose network part
+    carries the factor s_out."""
+    nz, ny, nx = shape
+    kw = {1: dict(force_kind=1, force_amp=1e-3, force_k=1),
+          2: dict(force_kind=2, force_amp=1e-3, force_k=1)}.get(force, {})
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25, **kw)
+    theta = inputs.glorot_params_net(inputs.net_widths(ocfg.Q, 0, "paper"), seed=7)
+    g = random_state(ocfg, 71, scale=0.03)
+    lam1 = random_state(ocfg, 72, scale=1.0)
+    kcfg, kth = kernel_emulation(ocfg, theta, prec)
+    want, wdth = oracle.step_adjoint(kcfg, g, lam1, kth)
+    got, gdth = gpu_adjoint(lbm, ocfg, g, lam1, theta, prec=prec)
+    e_lam, e_th = rel_l2(got, want), rel_l2(gdth, wdth)
+    print(f"{lat} {shape} x{batch} {prec}: lam rel L2 {e_lam:.2e}, dtheta rel L2 {e_th:.2e}")
+    assert e_lam < (2e-3 if prec == "bf16" else 3e-4)
+    assert e_th < (2e-2 if prec == "bf16" else 3e-3)
+
+
+def test_wide_adjoint_16bit_at_rest(lbm):
+    """A fluid at rest and zero biases: every pre-activation is exactly 0, where
+    the derivative is the slope, so b3's gradient is slope W4^T dY and the
+    weight gradients vanish."""
+    ocfg = oracle.Config(lattice="D3Q19", nx=6, ny=5, nz=4, batch=1, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25)
+    theta = inputs.glorot_params_net(inputs.net_widths(19, 0, "paper"), seed=7)
+    g = random_state(ocfg, 73) * 0.0
+    lam1 = random_state(ocfg, 74, scale=1.0)
+    want, wdth = oracle.step_adjoint(ocfg, g, lam1, theta.astype(np.float64))
+    got, gdth = gpu_adjoint(lbm, ocfg, g, lam1, theta, prec="bf16")
+    offs = _blocks(19)
+    b3, w4 = slice(offs[5], offs[6]), slice(offs[6], offs[7])
+    assert np.abs(wdth[b3]).max() > 0 and np.abs(wdth[w4]).max() == 0
+    assert rel_l2(gdth[b3], wdth[b3]) < 2e-2
+    assert np.abs(gdth[w4]).max() == 0
+    assert rel_l2(got, want) < 2e-3
+
+
+def test_wide_adjoint_sequence_packs_theta(lbm):
+    """A sequence packs theta once for all its steps; a later call with other
+    parameters uses those.  lam equals the step-by-step result bit for bit."""
+    ocfg = oracle.Config(lattice="D3Q19", nx=7, ny=6, nz=5, batch=1, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25)
+    L = lbm.Lattice(lib_config(ocfg, "bf16"))
+    states = [dev(to_shifted(random_state(ocfg, 80 + k), "D3Q19")) for k in range(3)]
+    lam = dev(to_shifted(random_state(ocfg, 90, scale=1.0), "D3Q19"))
+    for seed in (1, 2):
+        th = dev(inputs.glorot_params_net(inputs.net_widths(19, 0, "paper"), seed=seed))
+        a, b = lam.clone(), torch.empty_like(lam)
+        d = torch.zeros(L.n_param, dtype=torch.float32, device="cuda")
+        res = lbm.lbm_step_backward_seq(L.ctx, L.cfg, states, th, a, b, d, L.workspace())
+        l, e = lam, torch.zeros_like(d)
+        for s in reversed(states):
+            l, e = L.step_backward(s, th, l, dtheta=e)
+        assert torch.equal(res, l)
+        assert torch.equal(d, e)
+    L.close()
