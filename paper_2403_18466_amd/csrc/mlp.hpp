@@ -117,13 +117,26 @@ __device__ inline f4 mma_pair(f4 acc, typename Frag<P>::T a0, typename Frag<P>::
   }
 }
 
+// Wait states between a 16 x 16 x 32 product and a 16 x 16 x 16 one that
+// accumulates on its result.  A chain of one shape is forwarded by the
+// hardware; across the two shapes it is not, and the compiler inserts no
+// wait: issued back to back (or with one other product between), the second
+// one reads a stale accumulator (a chain of both over ones was wrong in every
+// result).  16 wait states cover the eight passes of the first product.
+// Chains with at least three other products between, whose sixteen clocks each
+// cover it, need no call.
+__device__ inline void mma_shape_wait(f4& acc) { asm volatile("s_nop 15" : "+v"(acc)); }
+
 // acc += sum over NC input chunks.
 template <int P, int NC>
 __device__ inline f4 mma_row(f4 acc, const typename Frag<P>::T* w, const typename Frag<P>::T* x) {
   int c = 0;
 #pragma unroll
   for (; c + 1 < NC; c += 2) acc = mma_pair<P>(acc, w[c], w[c + 1], x[c], x[c + 1]);
-  if constexpr (NC % 2 == 1) acc = mma_chunk<P>(acc, w[NC - 1], x[NC - 1]);
+  if constexpr (NC % 2 == 1) {
+    if constexpr (P != P_F32 && NC > 1) mma_shape_wait(acc);
+    acc = mma_chunk<P>(acc, w[NC - 1], x[NC - 1]);
+  }
   return acc;
 }
 
@@ -135,7 +148,10 @@ __device__ inline f4 mma_row_lds(f4 acc, const typename Frag<P>::T* w,
   int c = 0;
 #pragma unroll
   for (; c + 1 < NC; c += 2) acc = mma_pair<P>(acc, w[64 * c], w[64 * (c + 1)], x[c], x[c + 1]);
-  if constexpr (NC % 2 == 1) acc = mma_chunk<P>(acc, w[64 * (NC - 1)], x[NC - 1]);
+  if constexpr (NC % 2 == 1) {
+    if constexpr (P != P_F32 && NC > 1) mma_shape_wait(acc);
+    acc = mma_chunk<P>(acc, w[64 * (NC - 1)], x[NC - 1]);
+  }
   return acc;
 }
 

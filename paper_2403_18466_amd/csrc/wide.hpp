@@ -234,6 +234,37 @@ __device__ inline void store_rows(rsrc_t dst, const RowOffsets& r, const Item& t
                                           (int)(r.field + q * r.plane + r.zo[1] + r.yo[1]), 0);
 }
 
+// Byte offsets of one node per lane (any flat node index, so that no lane is
+// idle at the end of a row): the x, y and z parts of its own cell and its six
+// neighbours' in plane 0 of its field; population q's plane is q plane bytes
+// further on (a scalar offset).
+struct NodeOffsets {
+  int x, y, z;
+  unsigned xo[3], yo[3], zo[3];  // index 1 + c: coordinate minus c
+  __device__ inline void start(const Grid& G, int Q, unsigned node) {
+    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
+    unsigned r = node / nx;
+    x = (int)(node - r * nx);
+    unsigned s = r / ny;
+    y = (int)(r - s * ny);
+    const unsigned b = s / nz;
+    z = (int)(s - b * nz);
+#pragma unroll
+    for (int c = -1; c <= 1; ++c) {
+      xo[1 + c] = (unsigned)wrap_sub(x, c, G.nx) * 4u;
+      yo[1 + c] = (unsigned)wrap_sub(y, c, G.ny) * (nx * 4u);
+      zo[1 + c] = ((unsigned)wrap_sub(z, c, G.nz) + b * (unsigned)Q * nz) * (nx * ny * 4u);
+    }
+  }
+  // plane 0 offset of the cell population q is pulled from (and its adjoint
+  // pushed to)
+  template <class L>
+  __device__ inline int pull(int q) const {
+    return (int)(xo[1 + L::cx[q]] + yo[1 + L::cy[q]] + zo[1 + L::cz[q]]);
+  }
+  __device__ inline int at() const { return (int)(xo[1] + yo[1] + zo[1]); }
+};
+
 template <class L, int P>
 struct WideCfg {
   using WL = WideLayout<L::Q, P>;
@@ -441,10 +472,12 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
                   constexpr int k = u / GT, j = u % GT;
 #pragma unroll
                   for (int n = 0; n < NT; ++n) {
-                    if constexpr (k < NP)
+                    if constexpr (k < NP) {
                       acc[j][n] = mma_pair<P>(acc[j][n], f.a0, f.a1, h1[2 * k][n], h1[2 * k + 1][n]);
-                    else
+                    } else {
+                      if constexpr (P != P_F32 && GT * NT < 4) mma_shape_wait(acc[j][n]);
                       acc[j][n] = mma_chunk<P>(acc[j][n], f.a0, h1[WL::K2 - 1][n]);
+                    }
                   }
                   if constexpr (u == U2 - 1) {
 #pragma unroll
@@ -490,10 +523,12 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
                 constexpr int u = decltype(uc)::value, k = u / WL::T4, t4 = u % WL::T4;
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
-                  if constexpr (k < NP)
+                  if constexpr (k < NP) {
                     acc[t4][n] = mma_pair<P>(acc[t4][n], f.a0, f.a1, h3[2 * k][n], h3[2 * k + 1][n]);
-                  else
+                  } else {
+                    if constexpr (P != P_F32 && WL::T4 * NT < 4) mma_shape_wait(acc[t4][n]);
                     acc[t4][n] = mma_chunk<P>(acc[t4][n], f.a0, h3[WL::K4 - 1][n]);
+                  }
                 }
                 if constexpr (k == KU - 1) {
                   const int row = 16 * t4 + 4 * lg;
@@ -533,6 +568,10 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
 hipError_t wide_step_launch(bool d3q19, int prec, unsigned nb, hipStream_t s, const float* Ain,
                             float* Aout, const unsigned char* packed, Grid G, Force Fc,
                             float rho0, float omega, float knn, int per, int nitems, int nxc);
+// The 16-bit step by blocks of 64 nodes (wide_step16.hpp).
+hipError_t wide_step16_launch(bool d3q19, int prec, unsigned nwg, hipStream_t s, const float* Ain,
+                              float* Aout, const unsigned char* packed, Grid G, Force Fc,
+                              float rho0, float omega, float knn, int nblocks);
 hipError_t wide_pack_launch(int prec, unsigned blocks, hipStream_t s, const float* theta,
                             const int* idx, unsigned char* packed, int nw, int nb);
 

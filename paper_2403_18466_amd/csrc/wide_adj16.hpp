@@ -151,37 +151,6 @@ __device__ inline f4 mma32(u4 a, u4 b, f4 c) {
                                                   __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// Byte offsets of one node per lane (any flat node index, so that no lane is
-// idle at the end of a row): the x, y and z parts of its own cell and its six
-// neighbours' in plane 0 of its field; population q's plane is q plane bytes
-// further on (a scalar offset).
-struct NodeOffsets {
-  int x, y, z;
-  unsigned xo[3], yo[3], zo[3];  // index 1 + c: coordinate minus c
-  __device__ inline void start(const Grid& G, int Q, unsigned node) {
-    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
-    unsigned r = node / nx;
-    x = (int)(node - r * nx);
-    unsigned s = r / ny;
-    y = (int)(r - s * ny);
-    const unsigned b = s / nz;
-    z = (int)(s - b * nz);
-#pragma unroll
-    for (int c = -1; c <= 1; ++c) {
-      xo[1 + c] = (unsigned)wrap_sub(x, c, G.nx) * 4u;
-      yo[1 + c] = (unsigned)wrap_sub(y, c, G.ny) * (nx * 4u);
-      zo[1 + c] = ((unsigned)wrap_sub(z, c, G.nz) + b * (unsigned)Q * nz) * (nx * ny * 4u);
-    }
-  }
-  // plane 0 offset of the cell population q is pulled from (and its adjoint
-  // pushed to)
-  template <class L>
-  __device__ inline int pull(int q) const {
-    return (int)(xo[1 + L::cx[q]] + yo[1 + L::cy[q]] + zo[1 + L::cz[q]]);
-  }
-  __device__ inline int at() const { return (int)(xo[1] + yo[1] + zo[1]); }
-};
-
 template <class L, int P>
 __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
     const float* __restrict__ A, const float* __restrict__ lam1, float* __restrict__ lam0,
@@ -230,12 +199,16 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
   const unsigned bytes = total * (unsigned)Q * 4u, plane4 = (unsigned)G.plane * 4u;
   const rsrc_t rA = make_rsrc(A, bytes), rL1 = make_rsrc(lam1, bytes), rL0 = make_rsrc(lam0, bytes);
   float lam[Q];
+  // (cast, not pack2: where v is a product, fp16 rounds it once)
   auto put_row = [&](unsigned char* buf, const float (&v)[32]) {
+    using T = typename OpT<P>::T;
+    typedef T t2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       u4 o;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = pack2<P>(v[8 * g + 2 * k], v[8 * g + 2 * k + 1]);
+      for (int k = 0; k < 4; ++k)
+        o[k] = __builtin_bit_cast(unsigned, t2{(T)v[8 * g + 2 * k], (T)v[8 * g + 2 * k + 1]});
       *reinterpret_cast<u4*>(buf + (lane >> 4) * 1024 + (16 * g + (lane & 15)) * 16) = o;
     }
   };
@@ -317,8 +290,12 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
     });
   };
 
+  // (the whole offset in the vector part: a wide store must not be followed
+  // at once by a write to its data registers, and the compiler keeps that
+  // distance only where the scalar offset is no register.  With one, the first
+  // dword of some lanes was the next value's.)
   auto put_rec = [&](int blk, int n, u4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, myrec, slot16, (n * AJ::NREC + blk) * 1024, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, myrec, slot16 + (n * AJ::NREC + blk) * 1024, 0, 0);
   };
   // Results as operands, to LDS where a later product reads them (buf) and
   // to the record: a pair of tiles, or the half hh of a shared pair.  Only

@@ -308,6 +308,7 @@ def test_wide_unrolled_gradient(lbm):
     ("D2Q9", (1, 8, 8), 1, 1),      # exactly one workgroup of 64 nodes
     ("D3Q19", (5, 13, 1), 1, 0),    # one node more (65), a dimension of 1
     ("D3Q19", (3, 7, 31), 2, 2),    # 1302 nodes: several node ranges, fewer than 8
+    ("D3Q19", (15, 17, 17), 1, 0),  # 4335 nodes: eight ranges and more
 ])
 def test_wide_adjoint_16bit_edges(lbm, lat, shape, batch, force, prec):
     """The 16-bit adjoint where its node tiles, workgroups and node ranges
@@ -370,3 +371,41 @@ def test_wide_adjoint_sequence_packs_theta(lbm):
         assert torch.equal(res, l)
         assert torch.equal(d, e)
     L.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("lat,shape,batch,force", [
+    ("D2Q9", (1, 1, 3), 1, 0),      # a few nodes of one block
+    ("D2Q9", (1, 5, 13), 1, 1),     # 65 nodes: a second block with one node
+    ("D3Q19", (4, 5, 10), 3, 2),    # 600 nodes, three fields in one block range
+    ("D3Q19", (33, 32, 33), 1, 2),  # 545 blocks on 512 workgroups: some take a second one
+])
+def test_wide_step_16bit_blocks(lbm, lat, shape, batch, force, prec):
+    """The step by blocks of 64 nodes where its blocks and its workgroups' walks
+    end: 300 repeats give the same bits, and the result lies within half the
+    rounding effect of the kernels' scheme (as the other 16-bit rows)."""
+    nz, ny, nx = shape
+    kw = {1: dict(force_kind=1, force_amp=1e-3, force_k=1),
+          2: dict(force_kind=2, force_amp=1e-3, force_k=1)}.get(force, {})
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25, **kw)
+    theta = inputs.glorot_params_net(inputs.net_widths(ocfg.Q, 0, "paper"), seed=7)
+    g = random_state(ocfg, 75, scale=0.03)
+    L = lbm.Lattice(lib_config(ocfg, prec))
+    A, th = dev(to_shifted(g, lat)), dev(theta)
+    out = L.step(A, th, 1)
+    for _ in range(300):
+        again = L.step(A, th, 1)
+    assert torch.equal(out, again)
+    got = to_canonical(host(out), lat)
+    L.close()
+    oracle.set_threads(8)
+    try:
+        kcfg, kth = kernel_emulation(ocfg, theta, prec)
+        want = oracle.step(kcfg, g, kth)
+        exact = oracle.step(ocfg, g, theta.astype(np.float64))
+    finally:
+        oracle.set_threads(1)
+    gap, eff = np.linalg.norm(got - want), np.linalg.norm(want - exact)
+    print(f"{lat} {shape} x{batch} {prec}: |gpu - emulated| / rounding effect {gap / eff:.2e}")
+    assert gap < 0.5 * eff
