@@ -18,6 +18,7 @@
 #include "kernels_ref.hpp"
 #include "lbm.h"
 #include "wide.hpp"
+#include "wide_step16.hpp"
 #include "wide_adj16.hpp"
 #include "wide_bwd.hpp"
 
@@ -44,6 +45,7 @@ struct lbm_ctx {
   int* wide_idx;
   unsigned char* wide_packed;
   int wide_nw, wide_nb;
+  bool wide_blocks;  // the 16-bit step runs by blocks of 64 nodes
   // its adjoint: gather table and packed padded W, W^T and bias vectors
   int* wide_bidx;
   unsigned char* wide_bpacked;
@@ -207,13 +209,34 @@ std::vector<int> wide_bwd_index() {
 }
 
 template <int Q>
-std::vector<int> wide_index_p(int prec, int& packed_bytes) {
+std::vector<int> wide_index_p(int prec, bool blocks, int& packed_bytes) {
   if (prec == LBM_MLP_FP32) {
     packed_bytes = WideLayout<Q, P_F32>::packed_bytes;
     return wide_index<Q, P_F32>();
   }
+  // bf16 and fp16 share the layouts
+  if (blocks) {
+    packed_bytes = WideStep<Q>::packed_bytes;
+    return wide_step_index<Q>();
+  }
   packed_bytes = WideLayout<Q, P_BF16>::packed_bytes;
-  return wide_index<Q, P_BF16>();  // bf16 and fp16 share the layout
+  return wide_index<Q, P_BF16>();
+}
+
+// Which kernel runs the 16-bit wide step.  Both have a unit of work that
+// fills the chip once: eight 64-node row items per compute unit in 31 us for
+// wide_step_kernel, two blocks of 64 nodes per compute unit in 10 us (and 4
+// us of start) for wide_step16_kernel.  So the blocks win on small grids and
+// where rows are no multiple of 64 (D3Q19 bf16, row items / blocks: 32^3 33.5 /
+// 15.1 us, 48^3 64.9 / 37.0, 56^3 66.1 / 55.9, 80^3 208 / 154), the row items,
+// whose weights feed eight times the nodes per read, on the large regular ones
+// (64^3 66.1 / 81.0 us, 256^3 3.93 / 5.15 ms).
+bool wide_by_blocks(const lbm_config& c, int ncu) {
+  const long long nodes = (long long)c.batch * c.nx * c.ny * c.nz;
+  const long long items = (long long)c.batch * ((c.nx + 63) / 64) * c.ny * c.nz;
+  const long long rounds_items = (items + 8LL * ncu - 1) / (8LL * ncu);
+  const long long rounds_blocks = ((nodes + 63) / 64 + 2LL * ncu - 1) / (2LL * ncu);
+  return 10 * rounds_blocks + 4 < 31 * rounds_items;
 }
 
 lbm_status validate(const lbm_config* c) {
@@ -388,25 +411,38 @@ lbm_status wide_pack(lbm_ctx* ctx, const float* theta, hipStream_t s) {
   return LBM_OK;
 }
 
-template <class L, int P>
+template <class L>
 lbm_status launch_wide(lbm_ctx* ctx, const float* Ain, float* Aout, hipStream_t s) {
-  using C = WideCfg<L, P>;
   Grid G = grid_of(ctx->cfg);
-  int nxc = (G.nx + 63) / 64;
-  long long nitems = (long long)nxc * G.ny * G.nz * G.batch;
-  if (nitems >= (1LL << 31)) return fail(LBM_ERR_INVALID, "too many work items");
-  // one workgroup of 8 wavefronts per compute unit (the LDS holds one)
-  long long nb = ctx->ncu;
-  long long cap = (nitems + C::WAVES - 1) / C::WAVES;
-  if (nb > cap) nb = cap;
-  if (nb >= 16) nb -= nb % 8;
-  const long long per = (nitems + nb * C::WAVES - 1) / (nb * C::WAVES);
   const lbm_config& c = ctx->cfg;
-  hipError_t e = wide_step_launch(L::Q == 19, P, (unsigned)nb, s, Ain, Aout, ctx->wide_packed, G,
-                                  force_of(ctx), (float)c.rho0, (float)(1.0 / c.tau),
-                                  (float)(c.out_scale / c.tau), (int)per, (int)nitems, nxc);
+  const int prec = prec_of(c.mlp_prec);
+  hipError_t e;
+  if (!ctx->wide_blocks) {
+    using C = WideCfg<L, P_F32>;  // (wavefronts per workgroup, the same for every precision)
+    int nxc = (G.nx + 63) / 64;
+    long long nitems = (long long)nxc * G.ny * G.nz * G.batch;
+    if (nitems >= (1LL << 31)) return fail(LBM_ERR_INVALID, "too many work items");
+    // one workgroup of 8 wavefronts per compute unit (the LDS holds one)
+    long long nb = ctx->ncu;
+    long long cap = (nitems + C::WAVES - 1) / C::WAVES;
+    if (nb > cap) nb = cap;
+    if (nb >= 16) nb -= nb % 8;
+    const long long per = (nitems + nb * C::WAVES - 1) / (nb * C::WAVES);
+    e = wide_step_launch(L::Q == 19, prec, (unsigned)nb, s, Ain, Aout, ctx->wide_packed, G,
+                         force_of(ctx), (float)c.rho0, (float)(1.0 / c.tau),
+                         (float)(c.out_scale / c.tau), (int)per, (int)nitems, nxc);
+  } else {
+    // blocks of 64 nodes, two workgroups per compute unit (their LDS)
+    const long long nblocks = ((long long)G.plane * G.batch + 63) / 64;
+    long long nwg = 2LL * ctx->ncu;
+    if (nwg > nblocks) nwg = nblocks;
+    if (nwg >= 16) nwg = (nwg + 7) / 8 * 8;
+    e = wide_step16_launch(L::Q == 19, prec, (unsigned)nwg, s, Ain, Aout,
+                           ctx->wide_packed, G, force_of(ctx), (float)c.rho0,
+                           (float)(1.0 / c.tau), (float)(c.out_scale / c.tau), (int)nblocks);
+  }
   if (e != hipSuccess)
-    return fail(LBM_ERR_HIP, std::string("launch of wide_step_kernel: ") + hipGetErrorString(e));
+    return fail(LBM_ERR_HIP, std::string("launch of the wide-network step: ") + hipGetErrorString(e));
   return LBM_OK;
 }
 
@@ -414,11 +450,7 @@ template <class L>
 lbm_status one_step(lbm_ctx* ctx, const float* Ain, float* Aout, const float* theta,
                     hipStream_t s) {
   if (ctx->cfg.net == LBM_NET_LEAKY_300_300_100 && ctx->cfg.hidden != 0) {
-    switch (ctx->cfg.mlp_prec) {
-      case LBM_MLP_FP32: return launch_wide<L, P_F32>(ctx, Ain, Aout, s);
-      case LBM_MLP_BF16: return launch_wide<L, P_BF16>(ctx, Ain, Aout, s);
-      default: return launch_wide<L, P_F16>(ctx, Ain, Aout, s);
-    }
+    return launch_wide<L>(ctx, Ain, Aout, s);
   }
   switch (ctx->cfg.hidden) {
     case 0: return launch_bgk<L>(ctx, Ain, Aout, s);
@@ -567,6 +599,7 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
   ctx->wide_idx = nullptr;
   ctx->wide_packed = nullptr;
   ctx->wide_nw = ctx->wide_nb = 0;
+  ctx->wide_blocks = false;
   ctx->wide_bidx = nullptr;
   ctx->wide_bpacked = nullptr;
   ctx->mrt = nullptr;
@@ -604,8 +637,10 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
   }
   if (cfg->hidden != 0 && cfg->net == LBM_NET_LEAKY_300_300_100) {
     int pbytes = 0;
-    std::vector<int> idx = cfg->lattice == LBM_D2Q9 ? wide_index_p<9>(cfg->mlp_prec, pbytes)
-                                                     : wide_index_p<19>(cfg->mlp_prec, pbytes);
+    ctx->wide_blocks = cfg->mlp_prec != LBM_MLP_FP32 && wide_by_blocks(*cfg, ctx->ncu);
+    std::vector<int> idx = cfg->lattice == LBM_D2Q9
+                               ? wide_index_p<9>(cfg->mlp_prec, ctx->wide_blocks, pbytes)
+                               : wide_index_p<19>(cfg->mlp_prec, ctx->wide_blocks, pbytes);
     const int eb = cfg->mlp_prec == LBM_MLP_FP32 ? 4 : 2;
     ctx->wide_nb = cfg->lattice == LBM_D2Q9 ? WideLayout<9, P_BF16>::nbias
                                             : WideLayout<19, P_BF16>::nbias;

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "wide.hpp"
+#include "wide_step16.hpp"
 
 namespace lbm {
 
@@ -16,7 +17,7 @@ hipError_t step_one(unsigned nb, hipStream_t s, const float* Ain, float* Aout,
                     const unsigned char* packed, Grid G, Force Fc, float rho0, float omega,
                     float knn, int per, int nitems, int nxc) {
   hipLaunchKernelGGL((wide_step_kernel<L, P>), dim3(nb), dim3(WideCfg<L, P>::THREADS), 0, s, Ain,
-                     Aout, packed, G, Fc, rho0, omega, knn, per, nitems, nxc);
+                     Aout, packed, G, Fc, rho0, omega, knn, per, nitems, nxc, (int)nb);
   return hipGetLastError();
 }
 
@@ -31,6 +32,15 @@ hipError_t step_prec(int prec, unsigned nb, hipStream_t s, const float* Ain, flo
   }
 }
 
+template <class L, int P>
+hipError_t step16(unsigned nwg, hipStream_t s, const float* Ain, float* Aout,
+                  const unsigned char* packed, Grid G, Force Fc, float rho0, float omega,
+                  float knn, int nblocks) {
+  hipLaunchKernelGGL((wide_step16_kernel<L, P>), dim3(nwg), dim3(256), 0, s, Ain, Aout, packed, G,
+                     Fc, rho0, omega, knn, nblocks, (int)nwg);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t wide_step_launch(bool d3q19, int prec, unsigned nb, hipStream_t s, const float* Ain,
@@ -39,6 +49,18 @@ hipError_t wide_step_launch(bool d3q19, int prec, unsigned nb, hipStream_t s, co
   if (d3q19)
     return step_prec<D3Q19>(prec, nb, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, per, nitems, nxc);
   return step_prec<D2Q9>(prec, nb, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, per, nitems, nxc);
+}
+
+hipError_t wide_step16_launch(bool d3q19, int prec, unsigned nwg, hipStream_t s, const float* Ain,
+                              float* Aout, const unsigned char* packed, Grid G, Force Fc,
+                              float rho0, float omega, float knn, int nblocks) {
+  if (d3q19)
+    return prec == P_BF16
+               ? step16<D3Q19, P_BF16>(nwg, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, nblocks)
+               : step16<D3Q19, P_F16>(nwg, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, nblocks);
+  return prec == P_BF16
+             ? step16<D2Q9, P_BF16>(nwg, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, nblocks)
+             : step16<D2Q9, P_F16>(nwg, s, Ain, Aout, packed, G, Fc, rho0, omega, knn, nblocks);
 }
 
 hipError_t wide_pack_launch(int prec, unsigned blocks, hipStream_t s, const float* theta,

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
                                                         const unsigned char* __restrict__ packed,
                                                         Grid G, Force Fc, float rho0,
                                                         float omega, float knn, int per,
-                                                        int nitems, int nxc) {
+                                                        int nitems, int nxc, int nb) {
   using C = WideCfg<L, P>;
   using WL = typename C::WL;
   using F = typename Frag<P>::T;
@@ -303,12 +303,14 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
   __shared__ __attribute__((aligned(16))) float bias[WL::nbias];
   __shared__ __attribute__((aligned(16))) float tiles[C::WAVES * 64 * SX];
 
-  const int tid = threadIdx.x;
+  // (the builtins, not threadIdx and blockIdx: under this unit's options those
+  // are calls whose results the compiler takes for per-lane values)
+  const int tid = (int)__builtin_amdgcn_workitem_id_x();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, lg = lane >> 4, li = lane & 15;
   float* T = tiles + wave * 64 * SX;
 
-  const int nb = gridDim.x, bid = blockIdx.x;
+  const int bid = (int)__builtin_amdgcn_workgroup_id_x();
   const int lb = (nb % 8 == 0) ? (bid % 8) * (nb / 8) + bid / 8 : bid;
   const int it0 = (lb * C::WAVES + wave) * per;
 
