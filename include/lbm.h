@@ -142,7 +142,7 @@ typedef struct {
 /* Validate `cfg` and create a context holding a copy of it, bound to the
  * current device.  The context allocates one small device buffer
  * (96 KiB per field) for the float64 partial sums of lbm_moments and the
- * losses, and for D3Q19 one of 48 KiB for lbm_mrt_moment_sums; calls that
+ * losses, and for D3Q19 one of 190 KiB for lbm_mrt_moment_sums; calls that
  * use one context must therefore be ordered (one stream, or synchronised
  * streams).  With
  * LBM_NET_LEAKY_300_300_100 it also holds the weights in the kernel's

@@ -8,82 +8,166 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels_fwd.hpp"
+#include "wide.hpp"
 
 namespace lbm {
 
 constexpr int DIAG_BLOCKS = 64;
 constexpr int SF_PMAX = 8;
+constexpr int SF_THREADS = 512;
+constexpr int MRT_BLOCKS = 256;  // one per compute unit
 
-// Block-wide sum of v (256 threads) into red[0]; every thread must call it.
-__device__ inline double block_sum(double v, double* red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
+// Sum of v over the wavefront, in every lane (a fixed butterfly).
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+  return v;
 }
 
-// Separation l = blockIdx.y + 1; for every node, field and axis a < D the
-// longitudinal increment d = u_a(x + l e_a) - u_a(x) (periodic, in float64);
-// partial[(l - 1) * DIAG_BLOCKS + block][k]: sum of d^(k+1) for k < pmax,
-// then sum of |d|^(k+1).
-template <int D>
-__global__ __launch_bounds__(256) void structure_kernel(const float* __restrict__ u, Grid G,
-                                                        int pmax, double* __restrict__ partial) {
-  const int l = blockIdx.y + 1;
-  double s[SF_PMAX], sa[SF_PMAX];
+// A flat node index walked with a constant stride: its coordinates advance by
+// the stride's with carries instead of divisions.
+struct NodeWalk {
+  int x, y, z, b;
+  int sx, sy, sz, sb;
+  __device__ inline void start(const Grid& G, unsigned node, unsigned stride) {
+    split(G, node, x, y, z, b);
+    split(G, stride, sx, sy, sz, sb);
+  }
+  static __device__ inline void split(const Grid& G, unsigned n, int& x, int& y, int& z, int& b) {
+    unsigned r = n / (unsigned)G.nx;
+    x = (int)(n - r * (unsigned)G.nx);
+    unsigned t = r / (unsigned)G.ny;
+    y = (int)(r - t * (unsigned)G.ny);
+    b = (int)(t / (unsigned)G.nz);
+    z = (int)(t - (unsigned)b * (unsigned)G.nz);
+  }
+  __device__ inline void next(const Grid& G) {
+    x += sx;
+    int c = x >= G.nx;
+    x -= c ? G.nx : 0;
+    y += sy + c;
+    c = y >= G.ny;
+    y -= c ? G.ny : 0;
+    z += sz + c;
+    c = z >= G.nz;
+    z -= c ? G.nz : 0;
+    b += sb + c;
+  }
+};
+
+// Separations l0 + 1 .. l0 + LB (l0 = LB blockIdx.y); for every node, field
+// and axis a < D the longitudinal increment d = u_a(x + l e_a) - u_a(x)
+// (periodic, in float64); partial[(l - 1) * DIAG_BLOCKS + block][k]: sum of
+// d^(k+1) for k < PM, then sum of |d|^(k+1).
+//
+// Bound by the float64 additions and products: 5 + 9 per increment at PM = 6
+// (even powers are their own absolute values, and |d|^p is |d^p| exactly), of
+// 24 in the straightforward form, for 77 us of them at 128^3 and 32
+// separations.  A thread takes LB separations of a node, so that the node's
+// own values and coordinates are read and formed once.  128^3, 32 separations,
+// PM = 6: 168 us (620 us with one separation per thread, all eight powers and
+// 64-bit divisions).
+template <int D, int PM, int LB>
+__global__ __launch_bounds__(SF_THREADS) void structure_kernel(const float* __restrict__ u, Grid G,
+                                                               int lmax,
+                                                               double* __restrict__ partial) {
+  constexpr int NO = (PM + 1) / 2;  // odd powers
+  double s[LB][PM], sa[LB][NO];
 #pragma unroll
-  for (int p = 0; p < SF_PMAX; ++p) s[p] = sa[p] = 0.0;
-  const long long total = (long long)G.plane * G.batch;
-  for (long long n = blockIdx.x * 256LL + threadIdx.x; n < total;
-       n += (long long)gridDim.x * 256) {
-    int x, y, z, b;
-    decode(G, n, x, y, z, b);
-    const long long node = n - (long long)b * G.plane;
+  for (int j = 0; j < LB; ++j) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      int r[3] = {x, y, z};
-      const int dim = a == 0 ? G.nx : (a == 1 ? G.ny : G.nz);
-      r[a] = (r[a] + l) % dim;
-      const float* ua = u + ((long long)b * D + a) * G.plane;
-      const double d = (double)ua[((long long)r[2] * G.ny + r[1]) * G.nx + r[0]] - (double)ua[node];
-      double v = 1.0, va = 1.0;
+    for (int p = 0; p < PM; ++p) s[j][p] = 0.0;
 #pragma unroll
-      for (int p = 0; p < SF_PMAX; ++p) {
-        v *= d;
-        va *= d < 0.0 ? -d : d;
-        s[p] += v;
-        sa[p] += va;
+    for (int p = 0; p < NO; ++p) sa[j][p] = 0.0;
+  }
+  const int l0 = blockIdx.y * LB;
+  const unsigned total = (unsigned)G.plane * (unsigned)G.batch, stride = gridDim.x * SF_THREADS;
+  const unsigned first = blockIdx.x * SF_THREADS + threadIdx.x;
+  const int nx4 = G.nx * 4, nxy4 = G.nx * G.ny * 4, plane4 = G.plane * 4;
+  const rsrc_t src = make_rsrc(u, total * (unsigned)D * 4u);
+  auto at = [&](int off, int a) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, off, a * plane4, 0));
+  };
+  NodeWalk w;
+  if (first < total) w.start(G, first, stride);
+  for (unsigned n = first; n < total; n += stride) {
+    const int here = w.b * D * plane4 + w.z * nxy4 + w.y * nx4 + w.x * 4;
+    float own[D], other[LB][D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) own[a] = at(here, a);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      // (lmax is at most the smallest size: one wrap is enough; separations
+      // past lmax repeat the last one and are not written)
+      const int l = min(l0 + j + 1, lmax);
+      other[j][0] = at(here + (w.x + l >= G.nx ? (l - G.nx) * 4 : l * 4), 0);
+      other[j][1] = at(here + (w.y + l >= G.ny ? (l - G.ny) * nx4 : l * nx4), 1);
+      if constexpr (D == 3) other[j][2] = at(here + (w.z + l >= G.nz ? (l - G.nz) * nxy4 : l * nxy4), 2);
+    }
+#pragma unroll
+    for (int j = 0; j < LB; ++j)
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const double d = (double)other[j][a] - (double)own[a];
+        double v = d;
+#pragma unroll
+        for (int p = 0; p < PM; ++p) {
+          if (p > 0) v *= d;
+          s[j][p] += v;
+          if (p % 2 == 0) sa[j][p / 2] += __builtin_fabs(v);
+        }
       }
+    w.next(G);
+  }
+  // wavefront sums, then the wavefronts' in order
+  constexpr int NV = LB * (PM + NO), NW = SF_THREADS / 64;
+  __shared__ double red[NW][NV];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+#pragma unroll
+    for (int p = 0; p < PM; ++p) {
+      const double t = wave_sum(s[j][p]);
+      if (lane == 0) red[wave][j * (PM + NO) + p] = t;
+    }
+#pragma unroll
+    for (int p = 0; p < NO; ++p) {
+      const double t = wave_sum(sa[j][p]);
+      if (lane == 0) red[wave][j * (PM + NO) + PM + p] = t;
     }
   }
-  __shared__ double red[256];
-  double* out = partial + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * 2 * pmax;
-  for (int p = 0; p < pmax; ++p) {
-    const double t = block_sum(s[p], red), ta = block_sum(sa[p], red);
-    if (threadIdx.x == 0) {
-      out[p] = t;
-      out[pmax + p] = ta;
-    }
+  __syncthreads();
+  for (int k = threadIdx.x; k < LB * 2 * PM; k += SF_THREADS) {
+    const int j = k / (2 * PM), q = k % (2 * PM), p = q % PM;
+    if (l0 + j >= lmax) continue;
+    // |d|^p of an even p is d^p
+    const int from = j * (PM + NO) + (q < PM || p % 2 == 1 ? p : PM + p / 2);
+    double t = red[0][from];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) t += red[i][from];
+    partial[((size_t)(l0 + j) * gridDim.x + blockIdx.x) * 2 * PM + q] = t;
   }
 }
 
-// S[p][l] and Sabs[p][l] (row-major [pmax][lmax]) from the partials, summed
-// over the blocks in order and divided by the sample count.
+// S[p][l] and Sabs[p][l] (row-major [pmax][lmax]) from the partials of
+// separation l + 1 = blockIdx.x + 1, divided by the sample count: sixteen slices of
+// the blocks per entry, summed in slice order (4 us for 32 separations; 18.7
+// us with one thread walking all 64 blocks of an entry).
 static __global__ __launch_bounds__(256) void structure_reduce_kernel(const double* __restrict__ partial,
                                                                int nblk, int lmax, int pmax,
                                                                double inv_count,
                                                                double* __restrict__ S,
                                                                double* __restrict__ Sabs) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= lmax * 2 * pmax) return;
-  const int l = t / (2 * pmax), k = t % (2 * pmax);
+  static_assert(2 * SF_PMAX <= 16, "sixteen entries per separation");
+  __shared__ double red[16][16];
+  const int l = blockIdx.x, k = threadIdx.x & 15, sl = threadIdx.x >> 4;
   double acc = 0.0;
-  for (int b = 0; b < nblk; ++b) acc += partial[((long long)l * nblk + b) * 2 * pmax + k];
+  if (k < 2 * pmax)
+    for (int b = sl; b < nblk; b += 16) acc += partial[((long long)l * nblk + b) * 2 * pmax + k];
+  red[sl][k] = acc;
+  __syncthreads();
+  if (sl != 0 || k >= 2 * pmax) return;
+  for (int i = 1; i < 16; ++i) acc += red[i][k];
   if (k < pmax)
     S[k * lmax + l] = acc * inv_count;
   else
@@ -93,7 +177,7 @@ static __global__ __launch_bounds__(256) void structure_reduce_kernel(const doub
 // The MRT moment matrix M of the SI (D3Q19, velocity order of Table S1;
 // rows rho, e, eps, jx, qx, jy, qy, jz, qz, pxx, pixx, pww, piww, pxy, pyz,
 // pxz, mx, my, mz).
-static __constant__ signed char kMrtM[19][19] = {
+static constexpr signed char kMrtM[19][19] = {
     {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1},
     {-30, -11, -11, -11, -11, -11, -11, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8},
     {12, -4, -4, -4, -4, -4, -4, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1},
@@ -115,25 +199,58 @@ static __constant__ signed char kMrtM[19][19] = {
     {0, 0, 0, 0, 0, 0, 0, 0, -1, 1, 0, 1, -1, 1, -1, 0, -1, 1, 0},
 };
 
-// Moment i = blockIdx.y: with pre = A_n gathered at x, post = A_n1(x) (the
-// post-collision populations of x in the pull-shifted layout),
+// With pre = A_n gathered at x, post = A_n1(x) (the post-collision populations
+// of x in the pull-shifted layout), for every moment i
 //   m_diff = M_i (post - pre - f_ext),  m_neq = M_i (f_eq - pre),
-// partial[i][block][0..4] = sums of m_neq, m_diff, m_neq^2, m_neq m_diff,
+// partial[block][5 i + 0..4] = sums of m_neq, m_diff, m_neq^2, m_neq m_diff,
 // m_diff^2 (float64).
-static __global__ __launch_bounds__(256) void mrt_sums_kernel(const float* __restrict__ An,
-                                                       const float* __restrict__ An1, Grid G,
-                                                       Force Fc, float rho0,
-                                                       double* __restrict__ partial) {
+//
+// One pass over both states: a thread keeps the 95 sums (190 registers; one
+// wavefront per SIMD, with the next node's 38 loads in flight while this
+// one's moments are formed; M's zeros are skipped at compile time).  128^3:
+// 131 us (bound: 64 us of reading at the rate of a copy, 60 us of VALU
+// issue); 1,220 us as a workgroup row per moment, which read both states and
+// formed f_eq and f_ext nineteen times.
+static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void
+mrt_sums_kernel(const float* __restrict__ An, const float* __restrict__ An1, Grid G, Force Fc,
+                float rho0, double* __restrict__ partial) {
   using L = D3Q19;
-  const int i = blockIdx.y;
-  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  const long long total = (long long)G.plane * G.batch;
-  for (long long n = blockIdx.x * 256LL + threadIdx.x; n < total;
-       n += (long long)gridDim.x * 256) {
-    int x, y, z, b;
-    decode(G, n, x, y, z, b);
-    float g[19], geq[19], fe[19], F[3];
-    gather<L>(An, G, b, x, y, z, g);
+  double s[19][5];
+#pragma unroll
+  for (int i = 0; i < 19; ++i)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) s[i][k] = 0.0;
+  const unsigned total = (unsigned)G.plane * (unsigned)G.batch, stride = gridDim.x * 256u;
+  const unsigned bytes = total * 19u * 4u, plane4 = (unsigned)G.plane * 4u;
+  const rsrc_t r0 = make_rsrc(An, bytes), r1 = make_rsrc(An1, bytes);
+  float gn[19], pn[19];
+  int xn = 0, yn = 0, zn = 0;
+  auto load = [&](unsigned n) {
+    NodeOffsets o;
+    o.start(G, 19, n < total ? n : total - 1);
+    xn = o.x;
+    yn = o.y;
+    zn = o.z;
+#pragma unroll
+    for (int q = 0; q < 19; ++q)
+      gn[q] = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(r0, o.pull<L>(q), (int)(q * plane4), 0));
+#pragma unroll
+    for (int q = 0; q < 19; ++q)
+      pn[q] = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(r1, o.at(), (int)(q * plane4), 0));
+  };
+  unsigned n = blockIdx.x * 256u + threadIdx.x;
+  load(n);
+  for (; n < total; n += stride) {
+    float g[19], post[19], geq[19], fe[19], F[3];
+#pragma unroll
+    for (int q = 0; q < 19; ++q) {
+      g[q] = gn[q];
+      post[q] = pn[q];
+    }
+    const int x = xn, y = yn, z = zn;
+    load(n + stride);
     float drho, j[3];
     moments<L>(g, drho, j);
     const float rho = rho0 + drho, inv = 1.f / rho;
@@ -144,36 +261,63 @@ static __global__ __launch_bounds__(256) void mrt_sums_kernel(const float* __res
     const float dd = du[0] * (2.f * uv[0] + du[0]) + du[1] * (2.f * uv[1] + du[1]) +
                      du[2] * (2.f * uv[2] + du[2]);
     Unroll<L>::fext(rho, uv, du, dd, fe);
-    double md = 0.0, mn = 0.0;
+    double df[19], ne[19];
 #pragma unroll
     for (int q = 0; q < 19; ++q) {
-      const double post = An1[cell(G, b, q, 19, x, y, z)];
-      const double m = kMrtM[i][q];
-      md += m * (post - (double)g[q] - (double)fe[q]);
-      mn += m * ((double)geq[q] - (double)g[q]);
+      df[q] = (double)post[q] - (double)g[q] - (double)fe[q];
+      ne[q] = (double)geq[q] - (double)g[q];
     }
-    s[0] += mn;
-    s[1] += md;
-    s[2] += mn * mn;
-    s[3] += mn * md;
-    s[4] += md * md;
+    static_for<19>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      double md = 0.0, mn = 0.0;
+      static_for<19>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        if constexpr (kMrtM[i][q] != 0) {
+          constexpr double m = kMrtM[i][q];
+          md += m * df[q];
+          mn += m * ne[q];
+        }
+      });
+      s[i][0] += mn;
+      s[i][1] += md;
+      s[i][2] += mn * mn;
+      s[i][3] += mn * md;
+      s[i][4] += md * md;
+    });
   }
-  __shared__ double red[256];
-  for (int k = 0; k < 5; ++k) {
-    const double t = block_sum(s[k], red);
-    if (threadIdx.x == 0) partial[((long long)i * gridDim.x + blockIdx.x) * 5 + k] = t;
-  }
+  __shared__ double red[4][95];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 19; ++i)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const double t = wave_sum(s[i][k]);
+      if (lane == 0) red[wave][5 * i + k] = t;
+    }
+  __syncthreads();
+  if (threadIdx.x < 95)
+    partial[blockIdx.x * 95 + threadIdx.x] = ((red[0][threadIdx.x] + red[1][threadIdx.x]) +
+                                              red[2][threadIdx.x]) + red[3][threadIdx.x];
 }
 
-// stats[i][k] = sum over the blocks (in order) of partial[i][block][k].
-static __global__ __launch_bounds__(128) void mrt_reduce_kernel(const double* __restrict__ partial,
-                                                         int nblk, double* __restrict__ stats) {
-  const int t = threadIdx.x;
-  if (t >= 19 * 5) return;
-  const int i = t / 5, k = t % 5;
-  double acc = 0.0;
-  for (int b = 0; b < nblk; ++b) acc += partial[((long long)i * nblk + b) * 5 + k];
-  stats[t] = acc;
+// stats[t] = sum over the blocks of partial[block][t]: eight slices of the
+// blocks per entry, summed in slice order.
+static __global__ __launch_bounds__(768) void mrt_reduce_kernel(const double* __restrict__ partial,
+                                                                int nblk,
+                                                                double* __restrict__ stats) {
+  __shared__ double red[8][95];
+  const int sl = threadIdx.x / 96, t = threadIdx.x % 96;
+  if (t < 95) {
+    double acc = 0.0;
+    for (int b = sl; b < nblk; b += 8) acc += partial[b * 95 + t];
+    red[sl][t] = acc;
+  }
+  __syncthreads();
+  if (threadIdx.x < 95) {
+    double acc = red[0][threadIdx.x];
+    for (int k = 1; k < 8; ++k) acc += red[k][threadIdx.x];
+    stats[threadIdx.x] = acc;
+  }
 }
 
 }  // namespace lbm

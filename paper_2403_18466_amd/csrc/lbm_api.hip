@@ -534,6 +534,33 @@ lbm_status run_loss(lbm_ctx* ctx, const float* A, const float* ut, double* loss,
   return LBM_OK;
 }
 
+// ---------------------------------------------------- structure functions
+// Four separations per thread where that leaves workgroups for the whole chip
+// (64 per group of separations), else one.
+template <int D, int PM>
+void launch_structure_p(const float* u, Grid G, int lmax, double* part, hipStream_t s) {
+  if (lmax >= 16)
+    hipLaunchKernelGGL((structure_kernel<D, PM, 4>), dim3(DIAG_BLOCKS, (unsigned)((lmax + 3) / 4)),
+                       dim3(SF_THREADS), 0, s, u, G, lmax, part);
+  else
+    hipLaunchKernelGGL((structure_kernel<D, PM, 1>), dim3(DIAG_BLOCKS, (unsigned)lmax),
+                       dim3(SF_THREADS), 0, s, u, G, lmax, part);
+}
+
+template <int D>
+void launch_structure(const float* u, Grid G, int lmax, int pmax, double* part, hipStream_t s) {
+  switch (pmax) {
+    case 1: return launch_structure_p<D, 1>(u, G, lmax, part, s);
+    case 2: return launch_structure_p<D, 2>(u, G, lmax, part, s);
+    case 3: return launch_structure_p<D, 3>(u, G, lmax, part, s);
+    case 4: return launch_structure_p<D, 4>(u, G, lmax, part, s);
+    case 5: return launch_structure_p<D, 5>(u, G, lmax, part, s);
+    case 6: return launch_structure_p<D, 6>(u, G, lmax, part, s);
+    case 7: return launch_structure_p<D, 7>(u, G, lmax, part, s);
+    default: return launch_structure_p<D, 8>(u, G, lmax, part, s);
+  }
+}
+
 // ---------------------------------------------------- float64 reference
 template <class L, int H>
 lbm_status launch_ref(lbm_ctx* ctx, const double* Ain, double* Aout, const double* theta,
@@ -628,7 +655,7 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
     }
   }
   if (cfg->lattice == LBM_D3Q19) {
-    e = hipMalloc(&ctx->mrt, sizeof(double) * 19 * DIAG_BLOCKS * 5);
+    e = hipMalloc(&ctx->mrt, sizeof(double) * 95 * MRT_BLOCKS);
     if (e != hipSuccess) {
       lbm_destroy(ctx);
       return fail(LBM_ERR_HIP, std::string("hipMalloc of the moment-analysis buffer: ") +
@@ -1059,15 +1086,13 @@ lbm_status lbm_structure_functions(lbm_ctx* ctx, const float* u, int32_t lmax, i
                 "workspace smaller than lbm_structure_functions_workspace_bytes()");
   double* part = static_cast<double*>(ws);
   Grid G = grid_of(c);
-  dim3 grid(DIAG_BLOCKS, (unsigned)lmax);
   if (c.lattice == LBM_D2Q9)
-    hipLaunchKernelGGL(structure_kernel<2>, grid, dim3(256), 0, stream, u, G, pmax, part);
+    launch_structure<2>(u, G, lmax, pmax, part, stream);
   else
-    hipLaunchKernelGGL(structure_kernel<3>, grid, dim3(256), 0, stream, u, G, pmax, part);
+    launch_structure<3>(u, G, lmax, pmax, part, stream);
   LBM_LAUNCHED("structure_kernel");
   const double count = (double)G.plane * G.batch * lattice_d(c.lattice);
-  hipLaunchKernelGGL(structure_reduce_kernel, dim3(blocks_for((long long)lmax * 2 * pmax)), dim3(256),
-                     0, stream, part, DIAG_BLOCKS, lmax, pmax, 1.0 / count, S, S_abs);
+  hipLaunchKernelGGL(structure_reduce_kernel, dim3((unsigned)lmax), dim3(256), 0, stream, part, DIAG_BLOCKS, lmax, pmax, 1.0 / count, S, S_abs);
   LBM_LAUNCHED("structure_reduce_kernel");
   return LBM_OK;
   LBM_GUARD_END
@@ -1082,10 +1107,13 @@ lbm_status lbm_mrt_moment_sums(lbm_ctx* ctx, const float* A_n, const float* A_n1
   if (ctx->cfg.lattice != LBM_D3Q19)
     return fail(LBM_ERR_UNSUPPORTED, "the moment matrix M is given for D3Q19 only");
   Grid G = grid_of(ctx->cfg);
-  hipLaunchKernelGGL(mrt_sums_kernel, dim3(DIAG_BLOCKS, 19), dim3(256), 0, stream, A_n, A_n1, G,
-                     force_of(ctx), (float)ctx->cfg.rho0, ctx->mrt);
+  // one workgroup per compute unit, no more than there are nodes for
+  unsigned nb = blocks_for((long long)G.plane * G.batch);
+  if (nb > MRT_BLOCKS) nb = MRT_BLOCKS;
+  hipLaunchKernelGGL(mrt_sums_kernel, dim3(nb), dim3(256), 0, stream, A_n, A_n1, G, force_of(ctx),
+                     (float)ctx->cfg.rho0, ctx->mrt);
   LBM_LAUNCHED("mrt_sums_kernel");
-  hipLaunchKernelGGL(mrt_reduce_kernel, dim3(1), dim3(128), 0, stream, ctx->mrt, DIAG_BLOCKS, stats);
+  hipLaunchKernelGGL(mrt_reduce_kernel, dim3(1), dim3(768), 0, stream, ctx->mrt, (int)nb, stats);
   LBM_LAUNCHED("mrt_reduce_kernel");
   return LBM_OK;
   LBM_GUARD_END

@@ -89,3 +89,47 @@ def test_mrt_moment_sums(lbm, kind):
             assert abs(res[name][0] - 0.55) < 1e-4, (name, res[name])
     print(kind, {k: round(v[0], 4) for k, v in res.items() if not np.isnan(v[0])})
     L.close()
+
+
+@pytest.mark.parametrize("lat,shape,batch,lmax,pmax", [
+    ("D2Q9", (1, 2, 3), 1, 2, 1),        # fewer nodes than a wavefront
+    ("D2Q9", (1, 19, 41), 3, 19, 8),     # four separations per thread, the last group short
+    ("D3Q19", (17, 18, 37), 1, 16, 7),   # the smallest lmax of that form
+    ("D3Q19", (16, 50, 50), 1, 15, 5),   # the largest of the other; 40,000 nodes, 64 x 512 threads
+    ("D3Q19", (16, 50, 50), 1, 16, 3),   # every separation wraps in z at lmax = nz
+])
+def test_structure_functions_edges(lbm, lat, shape, batch, lmax, pmax):
+    """Grid and separation counts at the ends of the kernel's groups, every
+    power: within 1e-12 of the oracle (float64 sums in another order)."""
+    nz, ny, nx = shape
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch)
+    u = np.random.default_rng(95).normal(0, 0.05, (batch, ocfg.D, nz, ny, nx)).astype(np.float32)
+    want, wabs = oracle.structure_functions(ocfg, u.astype(np.float64), lmax, pmax)
+    L = lbm.Lattice(lib_config(ocfg))
+    S = torch.empty((pmax, lmax), dtype=torch.float64, device="cuda")
+    Sa = torch.empty_like(S)
+    ws = torch.empty(lbm.lbm_structure_functions_workspace_bytes(L.ctx, lmax, pmax) // 8,
+                     dtype=torch.float64, device="cuda")
+    lbm.lbm_structure_functions(L.ctx, L.cfg, torch.from_numpy(u).cuda(), lmax, pmax, S, Sa, ws)
+    assert np.all(np.abs(Sa.cpu().numpy() - wabs) <= 1e-12 * wabs)
+    assert np.all(np.abs(S.cpu().numpy() - want) <= 1e-12 * wabs)
+    L.close()
+
+
+@pytest.mark.parametrize("shape,batch", [((1, 1, 2), 1), ((3, 43, 2), 1), ((47, 40, 36), 1)])
+def test_mrt_moment_sums_edges(lbm, shape, batch):
+    """One block of a few nodes, a second block of two nodes (258), and more
+    nodes (67,680) than threads: the sums over the nodes against the oracle."""
+    nz, ny, nx = shape
+    ocfg = oracle.Config(lattice="D3Q19", nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55)
+    g = random_state(ocfg, 96, 0.03)
+    L = lbm.Lattice(lib_config(ocfg))
+    A = torch.from_numpy(to_shifted(g, "D3Q19").astype(np.float32)).cuda()
+    A1 = L.step(A, None, 1)
+    stats = torch.empty((19, 5), dtype=torch.float64, device="cuda")
+    lbm.lbm_mrt_moment_sums(L.ctx, A, A1, stats)
+    got = stats.cpu().numpy()
+    L.close()
+    want = oracle.mrt_moment_sums(ocfg, g.astype(np.float32).astype(np.float64),
+                                  to_canonical(A1.cpu().numpy().astype(np.float64), "D3Q19"))
+    assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
