@@ -2,26 +2,35 @@
 // (the products and the data flow are those listed in wide_bwd.hpp; the
 // float32 network keeps the chain of products there).
 //
-// Two kernels and a reduction per step (D3Q19 bf16, one step: 32^3 262 -> 70 us,
-// 60 x 64 x 52 1,330 -> 385 us against a chain of fourteen products on 64 x 64
+// Two kernels and a reduction per step (D3Q19 bf16, one step: 32^3 262 -> 62 us,
+// 60 x 64 x 52 1,330 -> 282 us against a chain of fourteen products on 64 x 64
 // tiles, which wrote every activation twice and read it three times):
 //
 //   wide_adj_data_kernel     64 nodes per workgroup, from the gather to the
 //       scatter of lam^n: the hidden layers are recomputed and differentiated
 //       with the activations of the 64 nodes in LDS (two buffers of 38 KB,
 //       two workgroups per compute unit) and the weights streamed from the
-//       L2 into registers in the order of use.  What bounds it: matrix-core
-//       and VALU issue in about equal parts (608 matrix instructions and
-//       about 750 VALU instructions of epilogue per 16 nodes).  31.6 us at
-//       32^3, 193 us at 60 x 64 x 52 (0.52 PFLOP/s; its parts took 167 us
-//       at 32^3 as separate products).
+//       L2 into registers in the order of use.  608 matrix instructions and
+//       about 750 VALU instructions of epilogue per 16 nodes (104 us at 60 x 64
+//       x 52 without the records' stores); 31 us at 32^3, which is one round
+//       of workgroups, about 165 us at 60 x 64 x 52 (0.61 PFLOP/s, 4 TB/s of
+//       records; its parts took 167 us at 32^3 as separate products).
 //   wide_adj_weight_kernel   the weight gradients, contractions over the
 //       nodes, from the activations the first kernel leaves in memory once
-//       (3.1 KB per node).  Bound by that read: 29 us at 32^3, 184 us at 60 x
-//       64 x 52 (3.5 TB/s; 72 and 375 us before).
-//   wide_adj_reduce_kernel   sums the node ranges' partial gradients: 9.4 us
-//       for 48 ranges (22.8 us at 32^3 and 57.4 us at 60 x 64 x 52 before,
-//       with 64 and 128 of them).
+//       (3.1 KB per node).  Bound by that read: 23 us at 32^3, 103 us at 60 x
+//       64 x 52 (6.2 TB/s; a streaming read reaches 6.3, and 7.0 with the
+//       non-temporal policy).
+//   wide_adj_reduce_kernel   sums the node ranges' partial gradients: 7.2 us
+//       for 32 ranges, 11.2 us for 64 (22.8 us at 32^3 and 57.4 us at 60 x 64
+//       x 52 before, with 64 and 128 of them).
+//
+// The record stores.  A wavefront stores, at each chunk of a product, the
+// operand of one node tile that the product reads anyway, a whole block at a
+// time, so that the stores run along with the matrix instructions.  (Stored
+// from the epilogues, all at once, the next weight fragments wait for them:
+// the counter of outstanding accesses is one.)  With that and the
+// non-temporal policy, which keeps a record larger than the last-level cache
+// from filling the L2 with lines to write back: 194 -> 165 us at 60 x 64 x 52.
 //
 // Work split of the first kernel.  A wavefront computes five of a layer's
 // twenty 16-row tiles for all 64 nodes, so a weight fragment (read from the
@@ -151,7 +160,7 @@ __device__ inline f4 mma32(u4 a, u4 b, f4 c) {
                                                   __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-template <class L, int P>
+template <class L, int P, bool NT>
 __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
     const float* __restrict__ A, const float* __restrict__ lam1, float* __restrict__ lam0,
     const unsigned char* __restrict__ packed, unsigned char* __restrict__ rec, Grid G, Force Fc,
@@ -259,9 +268,18 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
   // format's smallest positive number
   constexpr float kTiny = P == P_BF16 ? 0x1p-134f : 0x1p-25f;
 
+  // (the whole offset in the vector part: a wide store must not be followed
+  // at once by a write to its data registers, and the compiler keeps that
+  // distance only where the scalar offset is no register.  With one, the first
+  // dword of some lanes was the next value's.)
+  auto put_rec = [&](int blk, int n, u4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, myrec, slot16 + (n * AJ::NREC + blk) * 1024, 0,
+                                           NT ? kStoreNT : 0);
+  };
   // One product of the chain: acc[j][n] over the chunks of layer l, then
-  // ep(acc, n) per node tile.  rd(c, n): operand of chunk c and node tile n.
-  auto layer = [&](auto lc, auto&& rd, auto&& ep) {
+  // ep(acc, n) per node tile.  rd(c, n): operand of chunk c and node tile n;
+  // blk: record block of chunk 0.
+  auto layer = [&](auto lc, int blk, auto&& rd, auto&& ep) {
     constexpr int l = decltype(lc)::value, T = AJ::TPW[l], KCL = AJ::KC[l],
                   s0 = AJ::first_step(l);
     f4 acc[T][4];
@@ -275,12 +293,14 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
     static_for<KCL>([&](auto cc) {
       constexpr int c = decltype(cc)::value, s = s0 + c;
       issue(std::integral_constant<int, s + 2>{});
+      const u4 kept = rd(c, wave);
       static_for<4>([&](auto nc) {
         constexpr int n = decltype(nc)::value;
 #pragma unroll
         for (int j = 0; j < T; ++j) acc[j][n] = mma32<P>(ring[s % 3][j], xb[n], acc[j][n]);
         // the next chunk's operand, into the registers just consumed
         if constexpr (c + 1 < KCL) xb[n] = rd(c + 1, n);
+        if constexpr (n == 3) put_rec(blk + c, wave, kept);
         __builtin_amdgcn_sched_barrier(0);
       });
     });
@@ -290,36 +310,25 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
     });
   };
 
-  // (the whole offset in the vector part: a wide store must not be followed
-  // at once by a write to its data registers, and the compiler keeps that
-  // distance only where the scalar offset is no register.  With one, the first
-  // dword of some lanes was the next value's.)
-  auto put_rec = [&](int blk, int n, u4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, myrec, slot16 + (n * AJ::NREC + blk) * 1024, 0, 0);
-  };
-  // Results as operands, to LDS where a later product reads them (buf) and
-  // to the record: a pair of tiles, or the half hh of a shared pair.  Only
+  // Results as operands, to LDS: a pair of tiles, or the half hh of a shared
+  // pair.  Only
   // the second pair of wavefront 3 (`tail`) is a layer's last chunk, which
   // holds 16 features: half of the lanes, 512 bytes per node tile.
   const int p0 = AJ::pair0(wave), ph = AJ::half_pair(wave), hh = wave & 1;
   const int tail = wave == 3, tstride = tail ? 512 : 1024;
   const bool tlive = !tail || lane < 32;
-  auto put_pair = [&](unsigned char* buf, int rblk, int p, int n, u2 lo, u2 hi) {
+  auto put_pair = [&](unsigned char* buf, int p, int n, u2 lo, u2 hi) {
     const u4 o = {lo[0], lo[1], hi[0], hi[1]};
-    put_rec(rblk + p, n, o);
     *reinterpret_cast<u4*>(buf + p * 4096 + n * 1024 + l16) = o;
   };
-  auto put_tail = [&](unsigned char* buf, int rblk, int p, int n, u2 lo, u2 hi) {
+  auto put_tail = [&](unsigned char* buf, int p, int n, u2 lo, u2 hi) {
     const u4 o = {lo[0], lo[1], hi[0], hi[1]};
-    put_rec(rblk + p, n, o);
     if (tlive) *reinterpret_cast<u4*>(buf + p * 4096 + n * tstride + l16) = o;
   };
   // node tile n of a 20-tile layer
-  auto put5 = [&](unsigned char* buf, int rblk, int n, const u2 (&f)[5]) {
-    put_pair(buf, rblk, p0, n, f[0], f[1]);
-    put_tail(buf, rblk, p0 + 1, n, f[2], f[3]);
-    __builtin_amdgcn_raw_buffer_store_b64(f[4], myrec, slot16 + 8 * hh,
-                                          (n * AJ::NREC + rblk + ph) * 1024, 0);
+  auto put5 = [&](unsigned char* buf, int n, const u2 (&f)[5]) {
+    put_pair(buf, p0, n, f[0], f[1]);
+    put_tail(buf, p0 + 1, n, f[2], f[3]);
     *reinterpret_cast<u2*>(buf + ph * 4096 + n * 1024 + l16 + 8 * hh) = f[4];
   };
   // first feature of this lane's rows of tile j
@@ -364,36 +373,32 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
   for (int j = 0; j < 5; ++j) bv[j] = bias_of(W::fE1, feat5(j), W::D1);
   // H1 = leaky(X0 W1^T) (b1 in column Q, the constant column from the bias vector)
   layer(
-      std::integral_constant<int, 0>{},
-      [&](int, int n) {
-        const u4 v = read(bufQ, 0, n, false);
-        if (n == wave) put_rec(AJ::RX0, n, v);
-        return v;
-      },
+      std::integral_constant<int, 0>{}, AJ::RX0,
+      [&](int, int n) { return read(bufQ, 0, n, false); },
       [&](const f4 (&acc)[5][4], int n) {
         u2 f[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) f[j] = activate(acc[j][n], bv[j], m1[j]);
-        put5(bufP, AJ::RH1, n, f);
+        put5(bufP, n, f);
       });
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 5; ++j) bv[j] = bias_of(W::fB2, feat5(j), W::D2);
   // H2 = leaky(H1 W2^T + b2)
   layer(
-      std::integral_constant<int, 1>{}, [&](int c, int n) { return read(bufP, c, n, c == 9); },
+      std::integral_constant<int, 1>{}, AJ::RH1, [&](int c, int n) { return read(bufP, c, n, c == 9); },
       [&](const f4 (&acc)[5][4], int n) {
         u2 f[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) f[j] = activate(acc[j][n], bv[j], m2[j]);
-        put5(bufQ, AJ::RH2, n, f);
+        put5(bufQ, n, f);
       });
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 2; ++j) bv[j] = bias_of(W::fB3, 32 * wave + 8 * lg + 4 * j, W::D3);
   // H3 = leaky(H2 W3^T + b3): only its mask and the record are needed
   layer(
-      std::integral_constant<int, 2>{}, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
+      std::integral_constant<int, 2>{}, AJ::RH2, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
       [&](const f4 (&acc)[2][4], int n) {
         u2 f[2];
 #pragma unroll
@@ -402,34 +407,30 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
       });
   // dZ3 = (dY W4) . leaky'(H3)
   layer(
-      std::integral_constant<int, 3>{},
-      [&](int, int n) {
-        const u4 v = read(bufE, 0, n, false);
-        if (n == wave) put_rec(AJ::RDY, n, v);
-        return v;
-      },
+      std::integral_constant<int, 3>{}, AJ::RDY,
+      [&](int, int n) { return read(bufE, 0, n, false); },
       [&](const f4 (&acc)[2][4], int n) {
-        put_tail(bufP, AJ::RZ3, wave, n, masked(acc[0][n], m3[0], n), masked(acc[1][n], m3[1], n));
+        put_tail(bufP, wave, n, masked(acc[0][n], m3[0], n), masked(acc[1][n], m3[1], n));
       });
   __syncthreads();
   // dZ2 = (dZ3 W3) . leaky'(H2)
   layer(
-      std::integral_constant<int, 4>{}, [&](int c, int n) { return read(bufP, c, n, c == 3); },
+      std::integral_constant<int, 4>{}, AJ::RZ3, [&](int c, int n) { return read(bufP, c, n, c == 3); },
       [&](const f4 (&acc)[5][4], int n) {
         u2 f[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) f[j] = masked(acc[j][n], m2[j], n);
-        put5(bufQ, AJ::RZ2, n, f);
+        put5(bufQ, n, f);
       });
   __syncthreads();
   // dZ1 = (dZ2 W2) . leaky'(H1)
   layer(
-      std::integral_constant<int, 5>{}, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
+      std::integral_constant<int, 5>{}, AJ::RZ2, [&](int c, int n) { return read(bufQ, c, n, c == 9); },
       [&](const f4 (&acc)[5][4], int n) {
         u2 f[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) f[j] = masked(acc[j][n], m1[j], n);
-        put5(bufP, AJ::RZ1, n, f);
+        put5(bufP, n, f);
       });
   __syncthreads();
   // dX0 = dZ1 W1: wavefront w takes node tile w, rows of the inputs
@@ -440,6 +441,7 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
       constexpr int c = decltype(cc)::value, s = s0 + c;
       issue(std::integral_constant<int, s + 2>{});
       const u4 xv = read(bufP, c, wave, c == 9);
+      put_rec(AJ::RZ1 + c, wave, xv);
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[j] = mma32<P>(ring[s % 3][j], xv, acc[j]);
     });
@@ -464,168 +466,183 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradients.  Ten sets of 16 x 16 gradient tiles, each a product of
-// some record blocks over the nodes: dW2 in six (rows 0-7, 8-13, 14-18 x
-// columns 0-9, 10-18), dW3 in two, dW1 and dW4.  A workgroup takes one set
-// over one range of nodes and walks it 32 nodes at a time; the set's blocks
-// of the 32 nodes come into LDS by direct loads, two steps ahead in three
-// buffers.  The ten sets of a node range run on one XCD (workgroups go round
-// the eight XCDs), so that the blocks two or three sets share come from its
-// L2.
+// Weight gradients.  Four sets of 16 x 16 gradient tiles, each a product of
+// some record blocks over the nodes: dW2 in two (H1's chunks 0-4 and 5-9),
+// dW3, and dW1 with dW4; 14 to 16 of the fifty blocks each, so that sixty
+// are read for fifty.  A workgroup of eight wavefronts takes one set over
+// one range of nodes and walks it 32 nodes at a time; the set's blocks of
+// the 32 nodes come into LDS by direct loads, four steps ahead in five
+// buffers of 32 KB (one workgroup per compute unit).  The four sets of a
+// node range run on one XCD (workgroups go round the eight XCDs), so that
+// the blocks two sets share come from its L2.
+//
+// Bound by the read of the records.  Ten smaller sets (84 blocks for fifty)
+// with a barrier that waited for every load, one step in flight: 29 us at
+// 32^3, 183 at 60 x 64 x 52; four sets and four steps in flight 23 and 175;
+// with non-temporal loads 103 (see the rule at the launch).
 // ---------------------------------------------------------------------------
-struct WideSet {
-  int nrow, row0;  // row blocks: number, first record block
-  int ncol, col0;  // column blocks
-  int gr0, gc0;    // first gradient tile row and column
-  int rows, cols;  // tile rows and columns of the whole matrix
-  int slab;        // first slab tile of the matrix
-};
-constexpr int kWideSets = 10;
+constexpr int kWideSets = 4;
 
-template <int Q>
-__device__ constexpr WideSet wide_set(int s) {
+// record block that set S stages as its block k
+template <int Q, int S>
+__device__ constexpr int wide_staged(int k) {
   using A = WideAdj<Q>;
-  switch (s) {
-    case 0: return {4, A::RZ2, 5, A::RH1, 0, 0, 19, 19, A::G2};
-    case 1: return {4, A::RZ2, 5, A::RH1 + 5, 0, 10, 19, 19, A::G2};
-    case 2: return {3, A::RZ2 + 4, 5, A::RH1, 8, 0, 19, 19, A::G2};
-    case 3: return {3, A::RZ2 + 4, 5, A::RH1 + 5, 8, 10, 19, 19, A::G2};
-    case 4: return {3, A::RZ2 + 7, 5, A::RH1, 14, 0, 19, 19, A::G2};
-    case 5: return {3, A::RZ2 + 7, 5, A::RH1 + 5, 14, 10, 19, 19, A::G2};
-    case 6: return {4, A::RZ3, 5, A::RH2, 0, 0, 7, 19, A::G3};
-    case 7: return {4, A::RZ3, 5, A::RH2 + 5, 0, 10, 7, 19, A::G3};
-    case 8: return {1, A::RX0, 10, A::RZ1, 0, 0, 2, 19, A::G1};
-    default: return {1, A::RDY, 4, A::RH3, 0, 0, 2, 7, A::G4};
-  }
+  if (S < 2) return k < 10 ? A::RZ2 + k : A::RH1 + 5 * S + (k - 10);
+  if (S == 2) return k < 4 ? A::RZ3 + k : A::RH2 + (k - 4);
+  return k == 0 ? A::RX0 : (k < 11 ? A::RZ1 + k - 1 : (k == 11 ? A::RDY : A::RH3 + k - 12));
 }
 
-// vmcnt(n), other counters unconstrained
+// Waits until at most n of the wavefront's direct-to-LDS loads are in flight
+// and its LDS reads are done, then for the workgroup.  (__syncthreads would
+// wait for every load, and leave a single step in flight.)
 template <int n>
-__device__ inline void wait_loads() {
+__device__ inline void stage_barrier() {
   static_assert(n < 16, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | n);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070 | n);  // vmcnt(n) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-constexpr int kWideStageBytes = 11 * 2048;
+constexpr int kWideStageBytes = 16 * 2048;
 
-template <int Q, int P, int S>
+template <int Q, int P, bool NT, int S>
 __device__ __forceinline__ void wide_adj_weights(const unsigned char* __restrict__ rec,
                                                  float* __restrict__ slab, int step0, int steps,
                                                  unsigned char* st0, unsigned char* st1,
-                                                 unsigned char* st2) {
+                                                 unsigned char* st2, unsigned char* st3,
+                                                 unsigned char* st4) {
   using AJ = WideAdj<Q>;
-  constexpr WideSet D = wide_set<Q>(S);
-  constexpr int NB = D.nrow + D.ncol, NLD = (2 * NB + 3) / 4;
-  // wavefronts: 2 x 2 over (rows, columns); 1 x 4 over the columns where
-  // there is one row block
-  constexpr bool TALL = D.nrow > 1;
-  constexpr int NR = TALL ? D.nrow : 2, NC = TALL ? D.ncol : (2 * D.ncol + 3) / 4;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, lg = lane >> 4, li = lane & 15;
-  const int ur = TALL ? (wave >> 1) * NR : 0, uc = (TALL ? (wave & 1) : wave) * NC;
+  constexpr int NB = S < 2 ? 15 : (S == 2 ? 14 : 16), NLD = 4;  // blocks; loads per wavefront
+  constexpr int NR = S < 2 ? 5 : (S == 2 ? 4 : 2), NC = S < 3 ? 5 : 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)__builtin_amdgcn_workitem_id_x() >> 6);
+  const int lane = __builtin_amdgcn_workitem_id_x() & 63, lg = lane >> 4, li = lane & 15;
+  // the wavefront's tiles: first staged row and column unit (16 features;
+  // two per block), first gradient tile, the matrix (rows x cols tiles at
+  // slab tile g0)
+  int ru, cu, gr, gc, rows, cols, g0;
+  if constexpr (S < 2) {  // 4 x 2 wavefronts
+    ru = 5 * (wave >> 1), cu = 20 + 5 * (wave & 1);
+    gr = ru, gc = 10 * S + 5 * (wave & 1), rows = 19, cols = 19, g0 = AJ::G2;
+  } else if constexpr (S == 2) {  // 2 x 4
+    ru = 4 * (wave >> 2), cu = 8 + 5 * (wave & 3);
+    gr = ru, gc = 5 * (wave & 3), rows = 7, cols = 19, g0 = AJ::G3;
+  } else {  // five wavefronts on dW1, two on dW4; the eighth repeats the seventh's
+    const bool w1 = wave < 5;
+    const int w = w1 ? wave : (wave == 5 ? 0 : 1);
+    ru = w1 ? 0 : 22, cu = (w1 ? 2 : 24) + 4 * w;
+    gr = 0, gc = 4 * w, rows = wave < 7 ? 2 : 0, cols = w1 ? 19 : 7, g0 = w1 ? AJ::G1 : AJ::G4;
+  }
   f4 acc[NR][NC];
 #pragma unroll
   for (int i = 0; i < NR; ++i)
 #pragma unroll
     for (int j = 0; j < NC; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
-  // staged block k: 0..nrow-1 the rows, then the columns, each for the two
-  // node tiles of the step (1 KB per block and node tile); every wavefront
-  // issues NLD loads, the last one again where there are fewer
+  // each staged block holds the two node tiles of the step, 1 KB each; every
+  // wavefront issues NLD loads, the last one again where there are fewer
   const unsigned char* src = rec + (size_t)step0 * 2 * (AJ::NREC * 1024);
-  auto issue = [&](int i, unsigned char* st) {
-    if (i >= steps) return;
-    const rsrc_t r = make_rsrc(reinterpret_cast<const float*>(src + (size_t)i * 2 * (AJ::NREC * 1024)),
-                               2 * AJ::NREC * 1024);
+  int off[NLD], dst[NLD];
 #pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-      int k = wave + 4 * q;
-      if (k >= 2 * NB) k = 2 * NB - 1;
-      const int blk = k >> 1, nt = k & 1;
-      const int rb = blk < D.nrow ? D.row0 + blk : D.col0 + blk - D.nrow;
+  for (int q = 0; q < NLD; ++q) {
+    int k = wave + 8 * q;
+    if (k >= 2 * NB) k = 2 * NB - 1;
+    off[q] = ((k & 1) * AJ::NREC + wide_staged<Q, S>(k >> 1)) * 1024;
+    dst[q] = k * 1024;
+  }
+  // (steps past the range load nothing, from a resource of no bytes: the count
+  // of loads in flight is the same at every turn)
+  auto issue = [&](int i, unsigned char* st) {
+    const rsrc_t r = make_rsrc(reinterpret_cast<const float*>(src + (size_t)i * 2 * (AJ::NREC * 1024)),
+                               i < steps ? 2 * AJ::NREC * 1024 : 0);
+#pragma unroll
+    for (int q = 0; q < NLD; ++q)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          r, (__attribute__((address_space(3))) void*)(st + k * 1024), 16, lane * 16,
-          (nt * AJ::NREC + rb) * 1024, 0, 0);
-    }
+          r, (__attribute__((address_space(3))) void*)(st + dst[q]), 16, lane * 16, off[q], 0,
+          NT ? kStoreNT : 0);
   };
   // transposed read: this lane addresses the 8-byte row of node 4 (lane / 16)
   // + (lane % 16) / 4, features 4 a .. 4 a + 3 (a = lane % 4) of the unit
   const int a = lane & 3, nd = 4 * lg + (li >> 2);
   const int tr = 16 * (16 * (a >> 1) + (nd ^ (8 * (a >> 1)))) + 8 * (a & 1);
-  auto unit = [&](const unsigned char* st, int blk, int u) -> u4 {
-    const unsigned char* p = st + blk * 2048 + u * 512 + tr;
+  auto unit = [&](const unsigned char* st, int u) -> u4 {
+    const unsigned char* p = st + (u >> 1) * 2048 + (u & 1) * 512 + tr;
     const u2 v0 = read_tr<P>(p), v1 = read_tr<P>(p + 1024);
     return u4{v0[0], v0[1], v1[0], v1[1]};
   };
   auto compute = [&](const unsigned char* st) {
     u4 ra[NR];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) ra[i] = unit(st, (ur + i) >> 1, (ur + i) & 1);
+    for (int i = 0; i < NR; ++i) ra[i] = unit(st, ru + i);
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      int u = uc + j;
-      if (u >= 2 * D.ncol) u = 2 * D.ncol - 1;
-      const u4 cb = unit(st, D.nrow + (u >> 1), u & 1);
+      const u4 cb = unit(st, cu + j);
 #pragma unroll
       for (int i = 0; i < NR; ++i) acc[i][j] = mma32<P>(ra[i], cb, acc[i][j]);
     }
   };
   auto turn = [&](int i, const unsigned char* cur, unsigned char* fill) {
-    if (i + 1 < steps)
-      wait_loads<NLD>();
-    else
-      wait_loads<0>();
-    __syncthreads();
-    issue(i + 2, fill);
+    stage_barrier<3 * NLD>();
+    issue(i + 4, fill);
     compute(cur);
   };
   issue(0, st0);
   issue(1, st1);
-  for (int i = 0; i < steps; i += 3) {
-    turn(i, st0, st2);
-    if (i + 1 < steps) turn(i + 1, st1, st0);
-    if (i + 2 < steps) turn(i + 2, st2, st1);
+  issue(2, st2);
+  issue(3, st3);
+  // (whole rounds of the ring, then the rest: with an exit after every turn
+  // the compiler loses count of the loads and waits for all of them)
+  int i = 0;
+  for (; i + 5 <= steps; i += 5) {
+    turn(i, st0, st4);
+    turn(i + 1, st1, st0);
+    turn(i + 2, st2, st1);
+    turn(i + 3, st3, st2);
+    turn(i + 4, st4, st3);
   }
+  const int rest = steps - i;
+  if (rest > 0) turn(i, st0, st4);
+  if (rest > 1) turn(i + 1, st1, st0);
+  if (rest > 2) turn(i + 2, st2, st1);
+  if (rest > 3) turn(i + 3, st3, st2);
+  stage_barrier<0>();  // (the empty loads too are done before the LDS is given up)
 #pragma unroll
   for (int i = 0; i < NR; ++i)
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int r = D.gr0 + ur + i, c = D.gc0 + uc + j;
-      if (r < D.rows && c < D.cols && uc + j < 2 * D.ncol)
-        *reinterpret_cast<f4*>(slab + ((size_t)(D.slab + r * D.cols + c) * 64 + lane) * 4) = acc[i][j];
+      const int r = gr + i, c = gc + j;
+      if (r < rows && c < cols)
+        *reinterpret_cast<f4*>(slab + ((size_t)(g0 + r * cols + c) * 64 + lane) * 4) = acc[i][j];
     }
 }
 
 // grid: sets x splits; split k covers steps [k per, k per + per) of 32 nodes
 // and writes slab k.
-template <int Q, int P>
-__global__ __launch_bounds__(256, 2) void wide_adj_weight_kernel(
+template <int Q, int P, bool NT>
+__global__ __launch_bounds__(512) void wide_adj_weight_kernel(
     const unsigned char* __restrict__ rec, float* __restrict__ part, int nsteps, int per, int nsplit) {
   __shared__ __attribute__((aligned(16))) unsigned char st0[kWideStageBytes];
   __shared__ __attribute__((aligned(16))) unsigned char st1[kWideStageBytes];
   __shared__ __attribute__((aligned(16))) unsigned char st2[kWideStageBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char st3[kWideStageBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char st4[kWideStageBytes];
+  const int wg = (int)__builtin_amdgcn_workgroup_id_x();
   int set, split;
   if (nsplit % 8 == 0) {
-    const int i = blockIdx.x / 8;
-    split = blockIdx.x % 8 + 8 * (i / kWideSets);
+    const int i = wg / 8;
+    split = wg % 8 + 8 * (i / kWideSets);
     set = i % kWideSets;
   } else {
-    split = blockIdx.x / kWideSets;
-    set = blockIdx.x % kWideSets;
+    split = wg / kWideSets;
+    set = wg % kWideSets;
   }
   const int step0 = split * per, steps = min(per, nsteps - step0);
   float* slab = part + (size_t)split * (WideAdj<Q>::NG * 256);
   switch (set) {
-    case 0: wide_adj_weights<Q, P, 0>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 1: wide_adj_weights<Q, P, 1>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 2: wide_adj_weights<Q, P, 2>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 3: wide_adj_weights<Q, P, 3>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 4: wide_adj_weights<Q, P, 4>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 5: wide_adj_weights<Q, P, 5>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 6: wide_adj_weights<Q, P, 6>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 7: wide_adj_weights<Q, P, 7>(rec, slab, step0, steps, st0, st1, st2); break;
-    case 8: wide_adj_weights<Q, P, 8>(rec, slab, step0, steps, st0, st1, st2); break;
-    default: wide_adj_weights<Q, P, 9>(rec, slab, step0, steps, st0, st1, st2); break;
+    case 0: wide_adj_weights<Q, P, NT, 0>(rec, slab, step0, steps, st0, st1, st2, st3, st4); break;
+    case 1: wide_adj_weights<Q, P, NT, 1>(rec, slab, step0, steps, st0, st1, st2, st3, st4); break;
+    case 2: wide_adj_weights<Q, P, NT, 2>(rec, slab, step0, steps, st0, st1, st2, st3, st4); break;
+    default: wide_adj_weights<Q, P, NT, 3>(rec, slab, step0, steps, st0, st1, st2, st3, st4); break;
   }
 }
 

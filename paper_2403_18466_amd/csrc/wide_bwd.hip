@@ -84,6 +84,21 @@ GemmArgs args(const void* A, long long lda, const void* B, long long ldb, int M,
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
+// The records go through memory with the non-temporal policy where they do not
+// fit the last-level cache (256 MB): NT.
+template <class L, int P, bool NT>
+hipError_t run16_launch(hipStream_t s, const float* A, const float* lam1, float* lam0,
+                        const unsigned char* packed, unsigned char* rec, float* part, Grid G,
+                        Force Fc, float rho0, float omega, float knn, long long Np, int nsteps,
+                        int per, int nsplit) {
+  hipLaunchKernelGGL((wide_adj_data_kernel<L, P, NT>), dim3((unsigned)(Np / 64)), dim3(256), 0, s, A,
+                     lam1, lam0, packed, rec, G, Fc, rho0, omega, knn);
+  WB_CHECK(hipGetLastError());
+  hipLaunchKernelGGL((wide_adj_weight_kernel<L::Q, P, NT>), dim3((unsigned)(kWideSets * nsplit)),
+                     dim3(512), 0, s, rec, part, nsteps, per, nsplit);
+  return hipGetLastError();
+}
+
 // The 16-bit networks (wide_adj16.hpp): node-tile records at the start of the
 // workspace, then one gradient slab per node range.  The workspace keeps the
 // size of the product chain's layout, which holds every activation twice:
@@ -100,12 +115,20 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
   const size_t rec_bytes = (size_t)l.Np / 16 * (AJ::NREC * 1024), slab = (size_t)AJ::NG * 1024;
   unsigned char* rec = static_cast<unsigned char*>(ws);
   float* part = reinterpret_cast<float*>(rec + rec_bytes);
-  // Node ranges of the weight gradients: 48 x 10 workgroups fill the chip (two
-  // per compute unit) on the large grids; at least eight steps of 32 nodes
-  // per range on the small ones, whose cost is the slabs' write and sum.
+  // Node ranges of the weight gradients, four workgroups each, and the cache
+  // policy of the records.  Below the last-level cache's 256 MB (less what
+  // the fields need) the records are read back from it, and 32 ranges (half
+  // of the chip) read as fast as more while their slabs cost less to write
+  // and sum: D3Q19 bf16, whole adjoint, 32 ranges / 64: 32^3 62 / 66 us, 40^3
+  // (205 MB) 99 / 115 us; with the non-temporal policy 69 and 110 us.  Above
+  // it 64 ranges, one workgroup per compute unit, and non-temporal accesses:
+  // 44^3 (273 MB) 135 us (149 without, 144 with 32 ranges), 60 x 64 x 52 282 us
+  // (361; 301).  At least eight steps of 32 nodes per range on the small
+  // grids.
+  const bool nt = rec_bytes > ((size_t)224 << 20);
   const int nsteps = (int)(l.Np / 32);
   long long room = (long long)((l.total - rec_bytes) / slab), ns = (nsteps + 7) / 8;
-  if (ns > 48) ns = 48;
+  if (ns > (nt ? 64 : 32)) ns = nt ? 64 : 32;
   if (ns > room) ns = room;
   if (ns > 8) ns -= ns % 8;
   const int per = (int)((nsteps + ns - 1) / ns);
@@ -116,12 +139,8 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
                        theta, idx, packed, AJ::nw, W::nb);
     WB_CHECK(hipGetLastError());
   }
-  hipLaunchKernelGGL((wide_adj_data_kernel<L, P>), dim3((unsigned)(l.Np / 64)), dim3(256), 0, s, A,
-                     lam1, lam0, packed, rec, G, Fc, rho0, omega, knn);
-  WB_CHECK(hipGetLastError());
-  hipLaunchKernelGGL((wide_adj_weight_kernel<L::Q, P>), dim3((unsigned)(kWideSets * nsplit)),
-                     dim3(256), 0, s, rec, part, nsteps, per, nsplit);
-  WB_CHECK(hipGetLastError());
+  WB_CHECK((nt ? run16_launch<L, P, true> : run16_launch<L, P, false>)(
+      s, A, lam1, lam0, packed, rec, part, G, Fc, rho0, omega, knn, l.Np, nsteps, per, nsplit));
   hipLaunchKernelGGL(wide_adj_reduce_kernel<L::Q>, dim3(AJ::NG), dim3(256), 0, s, part, nsplit,
                      dtheta);
   return hipGetLastError();

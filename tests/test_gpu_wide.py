@@ -333,6 +333,27 @@ def test_wide_adjoint_16bit_edges(lbm, lat, shape, batch, force, prec):
     assert e_th < (2e-2 if prec == "bf16" else 3e-3)
 
 
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+def test_wide_adjoint_16bit_beyond_cache(lbm, prec):
+    """A batch whose records exceed the last-level cache (non-temporal
+    accesses, 64 node ranges) against its fields one by one (within it, 32
+    ranges): lam node by node the same bits; dtheta the same sums in another
+    order, some 100 float32 roundings of 2^-24 in quadrature (6e-7), bar 1e-5."""
+    cfg = dict(lattice="D2Q9", nx=157, ny=160, nz=1, tau=0.55, hidden=300, net="paper",
+               out_scale=0.25)
+    ocfg, one = oracle.Config(batch=3, **cfg), oracle.Config(batch=1, **cfg)
+    theta = inputs.glorot_params_net(inputs.net_widths(9, 0, "paper"), seed=7)
+    g = random_state(ocfg, 73, scale=0.03)
+    lam1 = random_state(ocfg, 74, scale=1.0)
+    got, gdth = gpu_adjoint(lbm, ocfg, g, lam1, theta, prec=prec)
+    sums = np.zeros_like(gdth)
+    for b in range(3):
+        lam, dth = gpu_adjoint(lbm, one, g[b:b + 1], lam1[b:b + 1], theta, prec=prec)
+        np.testing.assert_array_equal(got[b:b + 1], lam)
+        sums += dth
+    assert rel_l2(gdth, sums) < 1e-5
+
+
 def test_wide_adjoint_16bit_at_rest(lbm):
     """A fluid at rest and zero biases: every pre-activation is exactly 0, where
     the derivative is the slope, so b3's gradient is slope W4^T dY and the
