@@ -219,6 +219,68 @@ __device__ inline void scatter_rows(rsrc_t dst, const ItemRows& r, const Item& t
   }
 }
 
+// n / d for n < 2^31 by one high product: with 2^(s-1) < d <= 2^s and m =
+// ceil(2^(31+s) / d), m d exceeds 2^(31+s) by less than 2^s, and the quotient
+// by less than n 2^s / (d 2^(31+s)) < 1 / d.  (The compiler's division by a
+// number it does not know takes about 25 instructions.)
+struct FastDiv {
+  unsigned m;
+  int s;
+  FastDiv() = default;
+  explicit FastDiv(unsigned d) : s(0) {
+    while ((1ull << s) < d) ++s;
+    m = (unsigned)(((1ull << (31 + s)) + d - 1) / d);
+  }
+  __host__ __device__ inline unsigned quot(unsigned n) const {
+    return (unsigned)(((unsigned long long)(2u * n) * m) >> 32) >> s;
+  }
+};
+// the divisions of a flat node index
+struct FlatDiv {
+  FastDiv x, y, z;
+  FlatDiv() = default;
+  explicit FlatDiv(const Grid& G) : x(G.nx), y(G.ny), z(G.nz) {}
+};
+
+// Byte offsets of one node per lane (any flat node index, so that no lane is
+// idle at the end of a row): the x, y and z parts of its own cell and its six
+// neighbours' in plane 0 of its field; population q's plane is q plane bytes
+// further on (a scalar offset).
+struct NodeOffsets {
+  int x, y, z;
+  unsigned xo[3], yo[3], zo[3];  // index 1 + c: coordinate minus c
+  __device__ inline void start(const Grid& G, int Q, unsigned node) {
+    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
+    const unsigned r = node / nx, s = r / ny;
+    place(G, Q, node, r, s, s / nz);
+  }
+  __device__ inline void start(const Grid& G, int Q, unsigned node, const FlatDiv& f) {
+    const unsigned r = f.x.quot(node), s = f.y.quot(r);
+    place(G, Q, node, r, s, f.z.quot(s));
+  }
+  // node of row r, slab s (over all fields) and field b
+  __device__ inline void place(const Grid& G, int Q, unsigned node, unsigned r, unsigned s,
+                               unsigned b) {
+    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
+    x = (int)(node - r * nx);
+    y = (int)(r - s * ny);
+    z = (int)(s - b * nz);
+#pragma unroll
+    for (int c = -1; c <= 1; ++c) {
+      xo[1 + c] = (unsigned)wrap_sub(x, c, G.nx) * 4u;
+      yo[1 + c] = (unsigned)wrap_sub(y, c, G.ny) * (nx * 4u);
+      zo[1 + c] = ((unsigned)wrap_sub(z, c, G.nz) + b * (unsigned)Q * nz) * (nx * ny * 4u);
+    }
+  }
+  // plane 0 offset of the cell population q is pulled from (and its adjoint
+  // pushed to)
+  template <class L>
+  __device__ inline int pull(int q) const {
+    return (int)(xo[1 + L::cx[q]] + yo[1 + L::cy[q]] + zo[1 + L::cz[q]]);
+  }
+  __device__ inline int at() const { return (int)(xo[1] + yo[1] + zo[1]); }
+};
+
 template <class L, int q = 0>
 __device__ inline void gather_item(rsrc_t src, const Grid& G, const Item& t, float g[L::Q]) {
   if constexpr (q < L::Q) {
@@ -405,7 +467,7 @@ static __global__ __launch_bounds__(256) void diag_reduce_kernel(const double* _
 
 // BGK part: moments, equilibrium and Omega_q = (f^eq_q - f_q)/tau
 // (eq. bgk-sm with dt = 1, eq. feq).
-template <class L>
+template <class L, bool FUSED = false>
 __device__ inline void bgk_update(const float g[L::Q], float rho0, float omega, float upd[L::Q],
                                   float& rho, float u[3]) {
   float drho, j[3];
@@ -417,7 +479,10 @@ __device__ inline void bgk_update(const float g[L::Q], float rho0, float omega, 
   u[2] = L::D == 3 ? j[2] * inv : 0.f;
   const float uu = dot3<L>(u, u);
   float geq[L::Q];
-  Unroll<L>::feq(drho, rho, u, uu, geq);
+  if constexpr (FUSED)
+    Unroll<L>::feq_fused(drho, rho, j, inv, u, uu, geq);
+  else
+    Unroll<L>::feq(drho, rho, u, uu, geq);
 #pragma unroll
   for (int q = 0; q < L::Q; ++q) upd[q] = (geq[q] - g[q]) * omega;
 }
@@ -482,16 +547,27 @@ __device__ inline void smag_update(const float g[L::Q], float rho0, float tau, f
 
 // Projection of the whole update (kappa layer), then the EDM force, then
 // post = pre + update + force (eq. lbe-sm).
-template <class L>
+template <class L, bool FUSED = false>
 __device__ inline void finish_collision(const float g[L::Q], float upd[L::Q], float rho,
                                         const float u[3], const float F[3], bool forced,
                                         float post[L::Q]) {
-  project<L>(upd);
+  if constexpr (FUSED)
+    project_fused<L>(upd);
+  else
+    project<L>(upd);
   if (forced) {
     const float inv = __builtin_amdgcn_rcpf(rho);
     float du[3] = {F[0] * inv, F[1] * inv, F[2] * inv};
     const float u2[3] = {2.f * u[0] + du[0], 2.f * u[1] + du[1], 2.f * u[2] + du[2]};
     const float dd = dot3<L>(du, u2);
+    if constexpr (FUSED) {
+      float drho, j[3], pre[L::Q];
+      moments<L>(g, drho, j);
+#pragma unroll
+      for (int q = 0; q < L::Q; ++q) pre[q] = g[q] + upd[q];
+      Unroll<L>::fext_fused(rho, j, F, inv, u, du, dd, pre, post);
+      return;
+    }
     float fe[L::Q];
     Unroll<L>::fext(rho, u, du, dd, fe);
 #pragma unroll
@@ -581,7 +657,12 @@ __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // Workgroups are numbered so that each XCD walks one contiguous part of the
 // domain.
 // ---------------------------------------------------------------------------
-template <class L, int H>
+// Work items of the learned step: 64 consecutive x of one row; 64 or 16
+// consecutive nodes in flat order, whatever rows they belong to.
+// (FLAT16W: in workgroups of eight wavefronts.)
+enum StepItems { ROWS64, FLAT64, FLAT16, FLAT16W };
+
+template <class L, int H, int M = ROWS64>
 struct StepLds {
   // One row per node: the network input (g, the constant 1 of the layer-1
   // bias, zeros up to YC), then the network output y (YQ columns from YO),
@@ -597,7 +678,8 @@ struct StepLds {
   static constexpr bool ZERO_PAD = YO >= ZC;
   static constexpr int SX0 = YO + YQ + 4;
   static constexpr int SX = SX0 % 32 == 0 ? SX0 + 4 : SX0;  // row stride (floats)
-  static constexpr int per_wave = 64 * SX;
+  static constexpr int NODES = M >= FLAT16 ? 16 : 64;
+  static constexpr int per_wave = NODES * SX;
   // the layer-3 bias sits in the padding columns of the first 4 QB rows
   // (row 4 ob + g holds b3[16 ob + 4 g .. + 3]), not in registers
   static constexpr int B3 = YO + YQ;
@@ -606,6 +688,7 @@ struct StepLds {
   // the max-ILP scheduler otherwise takes to two: 8% slower), else no
   // constraint
   static constexpr int min_waves(int prec, bool forced) {
+    if (M >= FLAT16) return 1;
     return (!forced && ((L::Q == 19 && prec != P_F32) || (L::Q == 9 && prec == P_F32))) ? 3 : 1;
   }
   // wavefronts per workgroup: the 16-bit D2Q9 instances and the unforced
@@ -615,6 +698,7 @@ struct StepLds {
   // others run workgroups of 4 (the forced 16-bit D3Q19 instance needs 187
   // registers per lane, and at three wavefronts per SIMD it would spill)
   static constexpr int waves_per_block(int prec, bool forced) {
+    if (M >= FLAT16) return M == FLAT16 ? 4 : 8;
     return (prec == P_F32 || (forced && L::Q == 19)) ? 4 : (L::Q == 19 ? 12 : 16);
   }
 };
@@ -623,21 +707,27 @@ struct StepLds {
 // unforced instances leave out the force's registers: 108 instead of 120
 // registers per lane for the 16-bit D2Q9 instance, 159 instead of 187 for
 // D3Q19.
-template <class L, int H, int P, bool FORCED>
-__global__ __launch_bounds__((64 * StepLds<L, H>::waves_per_block(P, FORCED)))
-__attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void nlbm_step_kernel(
+template <class L, int H, int P, bool FORCED, int M>
+__global__ __launch_bounds__((64 * StepLds<L, H, M>::waves_per_block(P, FORCED)))
+__attribute__((amdgpu_waves_per_eu(StepLds<L, H, M>::min_waves(P, FORCED)))) void nlbm_step_kernel(
                                                         const float* __restrict__ Ain,
                                                         float* __restrict__ Aout,
                                                         const float* __restrict__ theta, Grid G,
                                                         Force Fc, float rho0, float omega,
-                                                        float knn, int nitems, int nxc) {
+                                                        float knn, int nitems, int nxc, FlatDiv fd) {
   using S = Shape<L::Q, H>;
-  using LD = StepLds<L, H>;
+  using LD = StepLds<L, H, M>;
   using F = typename Frag<P>::T;
   constexpr int Q = L::Q, WB = LD::waves_per_block(P, FORCED);
-  __shared__ __attribute__((aligned(16))) float lds[WB * LD::per_wave];
+  constexpr int NF = S::HB * S::KX + S::HB * S::HB + S::QB * S::HB;  // weight fragments
+  constexpr int frag_floats = NF * 64 * (int)sizeof(F) / 4;
+  __shared__ __attribute__((aligned(16))) float
+      lds[WB * LD::per_wave > frag_floats ? WB * LD::per_wave : frag_floats];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, lg = lane >> 4, li = lane & 15;
+  // this lane's node of the item (FLAT16: four lanes hold each node, and the
+  // first of them stores it)
+  const int nl = LD::NODES == 64 ? lane : li;
   float* X = lds + wave * LD::per_wave;
   float* Y = X + LD::YO;  // output columns of the same rows
 
@@ -667,12 +757,28 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void n
   const rsrc_t src = make_rsrc(Ain, bytes), dst = make_rsrc(Aout, bytes);
   // the first item's populations are loaded while the weights are staged
   ItemWalk cur, nxt;
-  float gn[Q];
+  const unsigned total = (unsigned)G.plane * (unsigned)G.batch, plane4 = (unsigned)G.plane * 4u;
+  float gn[Q], Fn[3] = {0.f, 0.f, 0.f};
+  int at = 0, atn = 0;  // flat items: byte offset of the node in plane 0
+  // (lanes past the last node read it; their results are never stored)
+  auto gather_flat = [&](int it) {
+    const unsigned n = (unsigned)(it * LD::NODES + nl);
+    NodeOffsets o;
+    o.start(G, Q, n < total ? n : total - 1, fd);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      gn[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                            src, o.pull<L>(q), (int)(q * plane4), 0));
+    if constexpr (FORCED) body_force(Fc, G, o.x, o.y, o.z, Fn);
+    return o.at();
+  };
   if (it0 < ib1) {
-    cur.start(it0, nxc, G);
-    {
+    if constexpr (M == ROWS64) {
+      cur.start(it0, nxc, G);
       const Item t0 = cur.item(G, lane);
       gather_rows<L>(src, ItemRows(G, Q, t0), t0, gn);
+    } else {
+      at = gather_flat(it0);
     }
   }
 
@@ -682,9 +788,6 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void n
   Weights<P, S> W;
   W.load_biases(theta);
   {
-    using F = typename Frag<P>::T;
-    constexpr int NF = S::HB * S::KX + S::HB * S::HB + S::QB * S::HB;
-    static_assert(NF * 64 * (int)sizeof(F) <= WB * LD::per_wave * 4, "fragment staging");
     F* fr = reinterpret_cast<F*>(lds);
     stage_weight_fragments<P, S, 64 * WB>(fr, theta);
     W.load_staged(fr);
@@ -709,7 +812,7 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void n
   // the input columns past the populations never change: a constant 1 for
   // the bias of layer 1, then zeros
 #pragma unroll
-  for (int k = Q; k < LD::YO; ++k) X[lane * LD::SX + k] = k == Q ? 1.f : 0.f;
+  for (int k = Q; k < LD::YO; ++k) X[nl * LD::SX + k] = k == Q ? 1.f : 0.f;
   if (lane < 4 * S::QB) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -725,26 +828,31 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void n
     // this item's populations go to the LDS tile; the next item's loads are
     // issued before the network runs
 #pragma unroll
-    for (int q = 0; q < Q; ++q) X[lane * LD::SX + q] = gn[q];
+    for (int q = 0; q < Q; ++q) X[nl * LD::SX + q] = gn[q];
+    float F3[3] = {Fn[0], Fn[1], Fn[2]};
     if (it + ST < ib1) {
-      nxt = cur;
-      if constexpr (ST > 1) {
-        nxt.advance(ST, nxc, G);
+      if constexpr (M == ROWS64) {
+        nxt = cur;
+        if constexpr (ST > 1) {
+          nxt.advance(ST, nxc, G);
+        } else {
+          nxt.next(nxc, G);
+        }
+        const Item tn = nxt.item(G, lane);
+        gather_rows<L>(src, ItemRows(G, Q, tn), tn, gn);
       } else {
-        nxt.next(nxc, G);
+        atn = gather_flat(it + ST);
       }
-      const Item tn = nxt.item(G, lane);
-      gather_rows<L>(src, ItemRows(G, Q, tn), tn, gn);
     }
     // the body force is read here, so that it arrives while the network runs
-    float F3[3] = {0.f, 0.f, 0.f};
-    if constexpr (FORCED) {
+    // (flat items: with the populations)
+    if constexpr (FORCED && M == ROWS64) {
       const Item tc = cur.item(G, lane);
       body_force(Fc, G, tc.x, tc.y, tc.z, F3);
     }
     wave_lds_sync();
 #pragma unroll
-    for (int jg = 0; jg < 4; ++jg) {
+    for (int jg = 0; jg < LD::NODES / 16; ++jg) {
       const int nrow = 16 * jg + li;
       F xin[S::KX];
 #pragma unroll
@@ -778,20 +886,32 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H>::min_waves(P, FORCED)))) void n
     wave_lds_sync();
 
     // node layout: BGK, network term, projection, force, store
-    const Item t = cur.item(G, lane);
     float g[Q], upd[Q], rho, u[3];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) g[q] = X[lane * LD::SX + q];
-    bgk_update<L>(g, rho0, omega, upd, rho, u);
+    for (int q = 0; q < Q; ++q) g[q] = X[nl * LD::SX + q];
+    // (16-node items: the sums' roundings written out, see feq_fused)
+    constexpr bool FUSED = LD::NODES == 16;
+    bgk_update<L, FUSED>(g, rho0, omega, upd, rho, u);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) upd[q] = __builtin_fmaf(knn, Y[lane * LD::SX + q], upd[q]);
+    for (int q = 0; q < Q; ++q) upd[q] = __builtin_fmaf(knn, Y[nl * LD::SX + q], upd[q]);
     float post[Q];
-    finish_collision<L>(g, upd, rho, u, F3, FORCED, post);
+    finish_collision<L, FUSED>(g, upd, rho, u, F3, FORCED, post);
     // the next item's populations arrived while the network ran
     wait_vmem();
-    if (t.active) store_rows<L, kStoreNT>(dst, ItemRows(G, Q, t), t, post);
+    if constexpr (M == ROWS64) {
+      const Item t = cur.item(G, lane);
+      if (t.active) store_rows<L, kStoreNT>(dst, ItemRows(G, Q, t), t, post);
+      cur = nxt;
+    } else {
+      if (lane < LD::NODES && (unsigned)(it * LD::NODES + nl) < total) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, post[q]), dst, at,
+                                                (int)(q * plane4), kStoreNT);
+      }
+      at = atn;
+    }
     wave_lds_sync();
-    cur = nxt;
   }
 }
 
@@ -810,9 +930,9 @@ inline unsigned persistent_grid(int ncu, int occ, long long units_per_block_min,
 }
 
 // Launch of the learned-collision step for (lattice, H, precision, forcing),
-// defined in nlbm_fwd.hip: a persistent grid over the nitems 64-node items.
+// defined in nlbm_fwd.hip with the rule for the work items: a persistent grid.
 hipError_t nlbm_fwd_launch(bool d3q19, int hidden, int prec, bool forced, int ncu, hipStream_t s,
                            const float* Ain, float* Aout, const float* theta, Grid G, Force Fc,
-                           float rho0, float omega, float knn, int nitems, int nxc);
+                           float rho0, float omega, float knn);
 
 }  // namespace lbm

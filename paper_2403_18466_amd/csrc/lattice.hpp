@@ -158,6 +158,40 @@ struct Unroll {
       Unroll<L, q + 1>::feq(drho, rho, u, uu, geq);
     }
   }
+  // c.v for v = p inv (rounded), as the compiler contracts cdot in the step's
+  // 64-node instances: the product of one component is fused into the sum.
+  // With the terms written out, every form of work item gives the same bits.
+  // (FORCE: v = du; there the compiler takes the other one for one velocity.)
+  template <bool FORCE = false>
+  static __device__ inline float cdot_fused(const float p[3], float inv, const float v[3]) {
+    constexpr int a = L::cx[q] != 0 ? 0 : 1, b = L::cz[q] != 0 ? 2 : 1;
+    if constexpr (L::cx[q] * L::cx[q] + L::cy[q] * L::cy[q] + L::cz[q] * L::cz[q] < 2) {
+      return cdot<L, q>(v);
+    } else {
+      constexpr bool na = comp<L>(q, a) < 0, nb = comp<L>(q, b) < 0;
+      constexpr bool first = L::D == 2 ? !na
+                             : b == 2  ? na && nb
+                                       : FORCE || !(na && !nb);
+      constexpr int f = first ? a : b, o = first ? b : a;
+      return __builtin_fmaf(comp<L>(q, f) < 0 ? -p[f] : p[f], inv,
+                            comp<L>(q, o) < 0 ? -v[o] : v[o]);
+    }
+  }
+  // feq with that c.u (u = j inv).
+  static __device__ inline void feq_fused(float drho, float rho, const float j[3], float inv,
+                                          const float u[3], float uu, float geq[L::Q]) {
+    if constexpr (q < L::Q) {
+      constexpr int nz = L::cx[q] * L::cx[q] + L::cy[q] * L::cy[q] + L::cz[q] * L::cz[q];
+      if constexpr (nz == 0) {
+        geq[q] = L::w[q] * __builtin_fmaf(rho, -1.5f * uu, drho);
+      } else {
+        const float cu = cdot_fused(j, inv, u);
+        float p = __builtin_fmaf(cu, __builtin_fmaf(4.5f, cu, 3.f), -1.5f * uu);
+        geq[q] = L::w[q] * __builtin_fmaf(rho, p, drho);
+      }
+      Unroll<L, q + 1>::feq_fused(drho, rho, j, inv, u, uu, geq);
+    }
+  }
   // Exact-difference-method force term of eq. fext,
   //   f^eq(rho, u + du) - f^eq(rho, u),  du = F / rho,
   // written as a difference so that no large terms cancel:
@@ -170,6 +204,19 @@ struct Unroll {
       float p = 3.f * cd + 4.5f * cd * (2.f * cu + cd) - 1.5f * dd;
       out[q] = L::w[q] * rho * p;
       Unroll<L, q + 1>::fext(rho, u, du, dd, out);
+    }
+  }
+  // post = pre + the force term, with fext's terms written out in the same way
+  // (du = F inv).
+  static __device__ inline void fext_fused(float rho, const float j[3], const float F[3], float inv,
+                                           const float u[3], const float du[3], float dd,
+                                           const float pre[L::Q], float post[L::Q]) {
+    if constexpr (q < L::Q) {
+      const float cu = cdot_fused(j, inv, u), cd = cdot_fused<true>(F, inv, du);
+      const float t = (4.5f * cd) * __builtin_fmaf(2.f, cu, cd);
+      const float p = __builtin_fmaf(-1.5f, dd, __builtin_fmaf(3.f, cd, t));
+      post[q] = __builtin_fmaf(L::w[q] * rho, p, pre[q]);
+      Unroll<L, q + 1>::fext_fused(rho, j, F, inv, u, du, dd, pre, post);
     }
   }
 };
@@ -195,6 +242,37 @@ __device__ inline void project(float v[L::Q]) {
       if (c < 0) d -= ka[a];
     }
     v[q] += d;
+  }
+}
+
+// The same with the first term of each population's sum written as the fused
+// multiply-add the compiler makes of it in the step's 64-node instances (k1's
+// product fused onto the rounded k2.., or the other way round).
+template <class L>
+__device__ inline void project_fused(float v[L::Q]) {
+  float s, m[3];
+  moments<L>(v, s, m);
+  const float k1 = -s * (1.f / L::Q);
+  const float c2 = 1.f / L::csum2;
+  const float ka[3] = {-m[0] * c2, -m[1] * c2, -m[2] * c2};
+#pragma unroll
+  for (int q = 0; q < L::Q; ++q) {
+    const bool k1_fused = L::D == 2 || (q >= 2 && q <= 5) || (q >= 11 && q <= 14);
+    float d = 0.f;
+    int n = 0;
+#pragma unroll
+    for (int a = 0; a < L::D; ++a) {
+      const int c = comp<L>(q, a);
+      if (c == 0) continue;
+      const float ma = c > 0 ? -m[a] : m[a];
+      if (n++ > 0)
+        d = __builtin_fmaf(ma, c2, d);
+      else if (k1_fused)
+        d = __builtin_fmaf(-s, 1.f / L::Q, c > 0 ? ka[a] : -ka[a]);
+      else
+        d = __builtin_fmaf(ma, c2, k1);
+    }
+    v[q] = n == 0 ? __builtin_fmaf(-s, 1.f / L::Q, v[q]) : v[q] + d;
   }
 }
 

@@ -395,7 +395,7 @@ lbm_status launch_nlbm(lbm_ctx* ctx, const float* Ain, float* Aout, const float*
   hipError_t e = nlbm_fwd_launch(L::Q == 19, H, prec_of(c.mlp_prec),
                                  c.force_kind != LBM_FORCE_NONE, ctx->ncu, s, Ain, Aout, theta, G,
                                  force_of(ctx), (float)c.rho0, (float)(1.0 / c.tau),
-                                 (float)(c.out_scale / c.tau), (int)nitems, nxc);
+                                 (float)(c.out_scale / c.tau));
   if (e != hipSuccess)
     return fail(LBM_ERR_HIP, std::string("launch of nlbm_step_kernel: ") + hipGetErrorString(e));
   return LBM_OK;

@@ -234,37 +234,6 @@ __device__ inline void store_rows(rsrc_t dst, const RowOffsets& r, const Item& t
                                           (int)(r.field + q * r.plane + r.zo[1] + r.yo[1]), 0);
 }
 
-// Byte offsets of one node per lane (any flat node index, so that no lane is
-// idle at the end of a row): the x, y and z parts of its own cell and its six
-// neighbours' in plane 0 of its field; population q's plane is q plane bytes
-// further on (a scalar offset).
-struct NodeOffsets {
-  int x, y, z;
-  unsigned xo[3], yo[3], zo[3];  // index 1 + c: coordinate minus c
-  __device__ inline void start(const Grid& G, int Q, unsigned node) {
-    const unsigned nx = G.nx, ny = G.ny, nz = G.nz;
-    unsigned r = node / nx;
-    x = (int)(node - r * nx);
-    unsigned s = r / ny;
-    y = (int)(r - s * ny);
-    const unsigned b = s / nz;
-    z = (int)(s - b * nz);
-#pragma unroll
-    for (int c = -1; c <= 1; ++c) {
-      xo[1 + c] = (unsigned)wrap_sub(x, c, G.nx) * 4u;
-      yo[1 + c] = (unsigned)wrap_sub(y, c, G.ny) * (nx * 4u);
-      zo[1 + c] = ((unsigned)wrap_sub(z, c, G.nz) + b * (unsigned)Q * nz) * (nx * ny * 4u);
-    }
-  }
-  // plane 0 offset of the cell population q is pulled from (and its adjoint
-  // pushed to)
-  template <class L>
-  __device__ inline int pull(int q) const {
-    return (int)(xo[1 + L::cx[q]] + yo[1 + L::cy[q]] + zo[1 + L::cz[q]]);
-  }
-  __device__ inline int at() const { return (int)(xo[1] + yo[1] + zo[1]); }
-};
-
 template <class L, int P>
 struct WideCfg {
   using WL = WideLayout<L::Q, P>;

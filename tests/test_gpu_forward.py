@@ -7,6 +7,8 @@ import oracle
 from lbm_cases import (plain_rounding_config, exact_config, fourier_state, kernel_emulation, lib_config,
                        params, random_state, rel_l2, to_canonical, to_shifted)
 
+from paper_2403_18466_amd import inputs
+
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
@@ -231,3 +233,41 @@ def test_nlbm_reduced_precision(lbm, prec, lat, shape, H):
     assert vs_plain < 2.0
     assert max_plain < (5e-3 if prec == "bf16" else 1e-3)
     assert max_exact < (5e-3 if prec == "bf16" else 1e-3)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("lat,shape,batch,force", [
+    ("D2Q9", (1, 29, 70), 80, 0),     # 2,030 nodes: 16-node items; 20: in workgroups of eight;
+    ("D2Q9", (1, 29, 70), 80, 1),     # 80: 64-node items in flat order
+    ("D2Q9", (1, 3, 64), 900, 1),     # ..., of one row
+    ("D3Q19", (5, 7, 33), 120, 0),
+    ("D3Q19", (5, 7, 33), 120, 2),
+    ("D3Q19", (2, 3, 64), 360, 2),
+])
+def test_step_item_forms(lbm, lat, shape, batch, force, prec):
+    """The forms of work item (16 or 64 nodes, of one row or in flat order)
+    that the size of the launch selects, against each other: the fields of a
+    large batch advanced together, a quarter of them, and one alone.  The same
+    arithmetic on the same numbers: at most a few roundings of 2^-24 in
+    differently fused sums, bar 1e-6 of the largest value."""
+    nz, ny, nx = shape
+    kw = {1: dict(force_kind=1, force_amp=1e-3, force_k=1),
+          2: dict(force_kind=2, force_amp=1e-3, force_k=1)}.get(force, {})
+
+    def step(g, n):
+        ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=n, tau=0.55, hidden=64,
+                             out_scale=0.25, **kw)
+        L = lbm.Lattice(lib_config(ocfg, prec))
+        out = host(L.step(dev(to_shifted(g, lat)), dev(theta), 1))
+        L.close()
+        return out
+
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55, hidden=64)
+    theta = inputs.random_params(ocfg.Q, 64, 5, scale=0.2)
+    g = random_state(ocfg, 17, scale=0.03)
+    full = step(g, batch)
+    bar = 1e-6 * np.abs(full).max()
+    quarter = max(1, batch // 4)
+    assert np.abs(step(g[:quarter], quarter) - full[:quarter]).max() <= bar
+    for b in (0, batch - 1):
+        assert np.abs(step(g[b:b + 1], 1) - full[b:b + 1]).max() <= bar
