@@ -26,7 +26,8 @@ hipError_t fwd_items(int ncu, hipStream_t s, const float* Ain, float* Aout, cons
   launched = rounds == 0 || nitems <= (long long)rounds * ncu * occ * wb;
   if (!launched) return hipSuccess;
   hipLaunchKernelGGL(kernel, dim3(persistent_grid(ncu, occ, wb, nitems)), dim3(64 * wb), 0, s,
-                     Ain, Aout, theta, G, Fc, rho0, omega, knn, nitems, nxc, FlatDiv(G));
+                     Ain, Aout, theta, G, Fc, rho0, omega, knn, nitems, nxc,
+                     StepDiv<M>::of(G));
   return hipGetLastError();
 }
 
