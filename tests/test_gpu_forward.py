@@ -271,3 +271,28 @@ def test_step_item_forms(lbm, lat, shape, batch, force, prec):
     assert np.abs(step(g[:quarter], quarter) - full[:quarter]).max() <= bar
     for b in (0, batch - 1):
         assert np.abs(step(g[b:b + 1], 1) - full[b:b + 1]).max() <= bar
+
+
+@pytest.mark.parametrize("nsteps", [1, 2, 3])
+@pytest.mark.parametrize("form", ["plain", "strided", "out", "out is A"])
+def test_step_preserves_state(lbm, form, nsteps):
+    """Lattice.step against the same number of single lbm_step calls on copies:
+    the same bits, the input untouched (unless it is given as out), and the
+    result in out for an odd number of steps."""
+    ocfg = oracle.Config(lattice="D2Q9", nx=37, ny=21, tau=0.6, hidden=0)
+    L = lbm.Lattice(lib_config(ocfg, "fp32"))
+    A0 = dev(to_shifted(random_state(ocfg, 19, scale=0.02), "D2Q9")).reshape(L.cfg.state_shape)
+    want = A0.clone()
+    for _ in range(nsteps):
+        want = lbm.lbm_step(L.ctx, L.cfg, want, L.empty_state(), None, 1)
+    A = A0.clone()
+    if form == "strided":
+        A = torch.stack([A0, A0], dim=-1)[..., 0]
+    out = {"out": L.empty_state(), "out is A": A}.get(form)
+    got = L.step(A, None, nsteps, out=out)
+    assert torch.equal(got, want)
+    if form != "out is A":
+        assert torch.equal(A, A0)
+    if form == "out" and nsteps % 2 == 1:
+        assert got.data_ptr() == out.data_ptr()
+    L.close()
