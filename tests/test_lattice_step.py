@@ -1,0 +1,84 @@
+"""Buffer handling of Lattice.step (host logic, CPU).
+
+The library is replaced by a stand-in on CPU tensors whose step adds 1 to
+every element of the buffer it reads, so the state after n steps is A + n.
+The reference is the plain form of the same call: n steps that alternate
+between a copy of A and out."""
+import ctypes
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+SHAPE = (1, 9, 1, 3, 4)
+
+
+class FakeLibrary:
+    """lbm_step as the library does it: the buffers must differ."""
+
+    def __init__(self):
+        self.calls = []
+
+    def lbm_state_elems(self, ctx):
+        return 108
+
+    def lbm_param_elems(self, ctx):
+        return 0
+
+    def lbm_step(self, ctx, A, B, theta, nsteps, stream):
+        a, b = (torch.frombuffer((ctypes.c_float * 108).from_address(p.value), dtype=torch.float32)
+                for p in (A, B))
+        self.calls.append(nsteps)
+        if A.value == B.value:
+            return 1
+        for _ in range(nsteps):
+            b.copy_(a + 1)
+            a, b = b, a
+        return 0
+
+    def lbm_last_error(self):
+        return b"A and B must differ"
+
+
+@pytest.fixture
+def lattice(monkeypatch):
+    from paper_2403_18466_amd import lbm
+
+    def ptr(t, dtype, numel=None, name="array", allow_none=False):
+        if t is None:
+            return None
+        if not t.is_contiguous() or t.dtype != dtype or t.numel() != numel:
+            raise ValueError(name)
+        return ctypes.c_void_p(t.data_ptr())
+
+    lib = FakeLibrary()
+    monkeypatch.setattr(lbm, "load_library", lambda: lib)
+    monkeypatch.setattr(lbm, "_ptr", ptr)
+    monkeypatch.setattr(lbm, "_stream", lambda s: None)
+    L = object.__new__(lbm.Lattice)
+    L.cfg = lbm.Config(nx=4, ny=3)
+    L.ctx, L.device, L.lib = None, torch.device("cpu"), lib
+    return L
+
+
+def plain(A, nsteps, out=None):
+    a = A.clone()
+    b = torch.empty(SHAPE) if out is None else out
+    for _ in range(nsteps):
+        b.copy_((a + 1).reshape(b.shape))
+        a, b = b, a
+    return a
+
+
+@pytest.mark.parametrize("nsteps", [0, 1, 2, 3, 6])
+@pytest.mark.parametrize("shape", [SHAPE, (9, 3, 4), (108,)])
+def test_result_shape(lattice, shape, nsteps):
+    """States are taken by their number of elements: the result has A's shape
+    after an even number of steps and out's after an odd one."""
+    A = torch.arange(108.0).reshape(shape)
+    A0 = A.clone()
+    want = plain(A0, nsteps)
+    got = lattice.step(A, None, nsteps)
+    assert torch.equal(A, A0)
+    assert got.shape == want.shape
+    assert torch.equal(got, want)
