@@ -426,11 +426,12 @@ class Lattice:
         b = self.empty_state() if out is None else out
         # The first step reads A and the others alternate between b and a new
         # buffer, so A needs no copy (842 -> 787 us for twelve steps of a 128^3
-        # field: the copy, and the lines it left behind in the cache).  A copy where A is no plain buffer or shares its memory with
-        # out, and for the large network, whose calls each pack the weights.
+        # field: the copy, and the lines it left behind in the cache).  A copy
+        # where A is no plain buffer or its memory overlaps out's (by address:
+        # two storages may share memory), and for the large network, whose
+        # calls each pack the weights.
         if (not isinstance(nsteps, int) or nsteps < 1 or self.cfg.net != "tanh"
-                or not A.is_contiguous()
-                or A.untyped_storage().data_ptr() == b.untyped_storage().data_ptr()):
+                or not A.is_contiguous() or abs(A.data_ptr() - b.data_ptr()) < A.nbytes):
             return lbm_step(self.ctx, self.cfg, A.clone(), b, theta, nsteps)
         lbm_step(self.ctx, self.cfg, A, b, theta, 1)
         if nsteps == 1:

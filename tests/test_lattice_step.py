@@ -82,3 +82,18 @@ def test_result_shape(lattice, shape, nsteps):
     assert torch.equal(A, A0)
     assert got.shape == want.shape
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("nsteps", [1, 2, 3])
+@pytest.mark.parametrize("first", [0, 108, 54])
+def test_out_in_the_same_memory(lattice, first, nsteps):
+    """out as a tensor of another storage on A's memory (an array taken over
+    by another library): all of A, none of it, half of it."""
+    base = torch.arange(3 * 108.0)
+    A = base[108:216].reshape(SHAPE)
+    out = torch.from_dlpack(base[first:first + 108])
+    want = plain(A, nsteps)
+    got = lattice.step(A, None, nsteps, out=out)
+    assert torch.equal(got.reshape(SHAPE), want)
+    if nsteps % 2 == 1:
+        assert got.data_ptr() == out.data_ptr()
