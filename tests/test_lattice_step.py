@@ -58,6 +58,7 @@ def lattice(monkeypatch):
     L = object.__new__(lbm.Lattice)
     L.cfg = lbm.Config(nx=4, ny=3)
     L.ctx, L.device, L.lib = None, torch.device("cpu"), lib
+    L.n_state, L.n_param = 108, 0
     return L
 
 
@@ -97,3 +98,22 @@ def test_out_in_the_same_memory(lattice, first, nsteps):
     assert torch.equal(got.reshape(SHAPE), want)
     if nsteps % 2 == 1:
         assert got.data_ptr() == out.data_ptr()
+
+
+@pytest.mark.parametrize("nsteps", [1, 2, 10])
+def test_arguments_are_marshalled_once(lattice, monkeypatch, nsteps):
+    """On small grids a call's time is the host's: every step after the first
+    goes in one library call, and each argument is checked and the stream
+    looked up once."""
+    from paper_2403_18466_amd import lbm
+    streams, names = [], []
+    check = lbm._ptr
+    monkeypatch.setattr(lbm, "_stream", lambda s: streams.append(s))
+    monkeypatch.setattr(lbm, "_ptr", lambda t, *a, **k: (names.append(id(t)), check(t, *a, **k))[1])
+    A = torch.arange(108.0).reshape(SHAPE)
+    got = lattice.step(A, None, nsteps)
+    assert torch.equal(got, A + nsteps)
+    assert sum(lattice.lib.calls) == nsteps and len(lattice.lib.calls) <= 2
+    assert len(streams) == 1
+    names = [n for n in names if n != id(None)]
+    assert len(names) == len(set(names))
