@@ -905,13 +905,13 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H, M>::min_waves(P, FORCED)))) voi
     float g[Q], upd[Q], rho, u[3];
 #pragma unroll
     for (int q = 0; q < Q; ++q) g[q] = X[nl * LD::SX + q];
-    // (16-node items: the sums' roundings written out, see feq_fused)
-    constexpr bool FUSED = LD::NODES == 16;
-    bgk_update<L, FUSED>(g, rho0, omega, upd, rho, u);
+    // (the sums' roundings are written out, see feq_fused: every form of work
+    // item gives the same bits)
+    bgk_update<L, true>(g, rho0, omega, upd, rho, u);
 #pragma unroll
     for (int q = 0; q < Q; ++q) upd[q] = __builtin_fmaf(knn, Y[nl * LD::SX + q], upd[q]);
     float post[Q];
-    finish_collision<L, FUSED>(g, upd, rho, u, F3, FORCED, post);
+    finish_collision<L, true>(g, upd, rho, u, F3, FORCED, post);
     // the next item's populations arrived while the network ran
     wait_vmem();
     if constexpr (M == ROWS64) {

@@ -158,10 +158,13 @@ struct Unroll {
       Unroll<L, q + 1>::feq(drho, rho, u, uu, geq);
     }
   }
-  // c.v for v = p inv (rounded), as the compiler contracts cdot in the step's
-  // 64-node instances: the product of one component is fused into the sum.
-  // With the terms written out, every form of work item gives the same bits.
-  // (FORCE: v = du; there the compiler takes the other one for one velocity.)
+  // c.v for v = p inv (rounded), with the product of one component fused into
+  // the sum: which one is written out, not left to the compiler, so that every
+  // form of the learned step's work items gives the same bits.  (Left to it,
+  // the float32 forced D2Q9 instances of two forms differed by a last place.)
+  // The choice is the one ROCm 7.2's compiler makes for 64-node row items,
+  // whose results thus stay as they were; for v = du (FORCE) it takes the
+  // other product for one velocity.
   template <bool FORCE = false>
   static __device__ inline float cdot_fused(const float p[3], float inv, const float v[3]) {
     constexpr int a = L::cx[q] != 0 ? 0 : 1, b = L::cz[q] != 0 ? 2 : 1;
@@ -245,9 +248,9 @@ __device__ inline void project(float v[L::Q]) {
   }
 }
 
-// The same with the first term of each population's sum written as the fused
-// multiply-add the compiler makes of it in the step's 64-node instances (k1's
-// product fused onto the rounded k2.., or the other way round).
+// The same with the first term of each population's sum written as a fused
+// multiply-add, for the same reason as cdot_fused: k1's product fused onto the
+// rounded k2.., or the other way round.
 template <class L>
 __device__ inline void project_fused(float v[L::Q]) {
   float s, m[3];

@@ -41,9 +41,9 @@ hipError_t fwd_items(int ncu, hipStream_t s, const float* Ain, float* Aout, cons
 // per step, 64 / 16 nodes: D2Q9 64^2 fp32 H = 32 8.2 / 5.2, bf16 H = 64 13.2
 // / 6.7, 256^2 13.8 / 9.3, 512 x 256 14.2 / 12.5 (two items each; at four,
 // 512^2, 14.8 / 18.7); D3Q19 bf16 16^3 15.6 / 8.1, 32^3 16.1 / 8.9.
-// The collision's sums have their roundings written out in the 16-node
-// instances, as the compiler contracts them in the 64-node ones: a network
-// rounded to 16 bits makes 1e-5 of a last-bit difference within ten steps.
+// All forms give the same bits: the collision's sums have their roundings
+// written out (a network rounded to 16 bits makes 1e-5 of a last-bit
+// difference within ten steps).
 //
 // Else 64 nodes: of one row, whose addresses are scalar but for the x part, or
 // in flat order, where no lane is idle at the rows' ends and the addresses

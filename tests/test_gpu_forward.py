@@ -296,3 +296,41 @@ def test_step_preserves_state(lbm, form, nsteps):
     if form == "out" and nsteps % 2 == 1:
         assert got.data_ptr() == out.data_ptr()
     L.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("lat,shape,batch,force", [
+    ("D2Q9", (1, 29, 70), 80, 0),     # 162,400 nodes: 64-node items in flat order; 20 fields:
+    ("D2Q9", (1, 29, 70), 80, 1),     # 16-node items in workgroups of eight, one: of four
+    ("D2Q9", (1, 3, 64), 900, 0),     # ..., of one row
+    ("D2Q9", (1, 3, 64), 900, 1),
+    ("D3Q19", (5, 7, 33), 120, 0),
+    ("D3Q19", (5, 7, 33), 120, 2),
+    ("D3Q19", (2, 3, 64), 360, 0),
+    ("D3Q19", (2, 3, 64), 360, 2),
+])
+def test_step_item_forms_same_bits(lbm, lat, shape, batch, force, H, prec):
+    """The forms of work item round alike: the fields of a large batch advanced
+    together, a quarter of them, and one alone give the same bits (three
+    steps, so that a difference of the 16-bit networks' inputs would show)."""
+    nz, ny, nx = shape
+    kw = {1: dict(force_kind=1, force_amp=1e-3, force_k=1),
+          2: dict(force_kind=2, force_amp=1e-3, force_k=1)}.get(force, {})
+    theta = inputs.random_params(9 if lat == "D2Q9" else 19, H, 5, scale=0.2)
+
+    def step(g, n):
+        ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=n, tau=0.55, hidden=H,
+                             out_scale=0.25, **kw)
+        L = lbm.Lattice(lib_config(ocfg, prec))
+        out = host(L.step(dev(to_shifted(g, lat)), dev(theta), 3))
+        L.close()
+        return out
+
+    g = random_state(oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55), 17,
+                     scale=0.03)
+    full = step(g, batch)
+    quarter = batch // 4
+    np.testing.assert_array_equal(step(g[:quarter], quarter), full[:quarter])
+    for b in (0, batch - 1):
+        np.testing.assert_array_equal(step(g[b:b + 1], 1), full[b:b + 1])
