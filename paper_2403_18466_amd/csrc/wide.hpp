@@ -234,6 +234,48 @@ __device__ inline void store_rows(rsrc_t dst, const RowOffsets& r, const Item& t
                                           (int)(r.field + q * r.plane + r.zo[1] + r.yo[1]), 0);
 }
 
+// c_q . du of the force term, du = F / rho, for the populations with two
+// moving components: one of the two products is fused with the sum.  Which one
+// is written out, so that the rounding does not depend on the compiler's
+// choice (the 16-bit rounding of the next step's network input carries a
+// difference in the last place on).
+template <class L, int q>
+__device__ inline float force_dot(const float F[3], const float du[3], float inv) {
+  constexpr int c[3] = {L::cx[q], L::cy[q], L::cz[q]};
+  constexpr int i = c[0] != 0 ? 0 : 1, j = c[2] != 0 ? 2 : 1;  // first, last moving component
+  if constexpr ((c[0] != 0) + (c[1] != 0) + (c[2] != 0) < 2) {
+    return cdot<L, q>(du);
+  } else if constexpr (c[i] < 0 && c[j] < 0) {
+    return __builtin_fmaf(-inv, F[i], -du[j]);
+  } else {
+    return __builtin_fmaf(c[j] > 0 ? inv : -inv, F[j], c[i] > 0 ? du[i] : -du[i]);
+  }
+}
+
+// finish_collision with the force term in that form, for both kernels of the
+// step (which give the same bits).
+template <class L>
+__device__ inline void finish_wide(const float g[L::Q], float upd[L::Q], float rho,
+                                   const float u[3], const float F[3], bool forced,
+                                   float post[L::Q]) {
+  project<L>(upd);
+  if (forced) {
+    const float inv = __builtin_amdgcn_rcpf(rho);
+    const float du[3] = {F[0] * inv, F[1] * inv, F[2] * inv};
+    const float u2[3] = {2.f * u[0] + du[0], 2.f * u[1] + du[1], 2.f * u[2] + du[2]};
+    const float dd = dot3<L>(du, u2);
+    static_for<L::Q>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      const float cu = cdot<L, q>(u), cd = force_dot<L, q>(F, du, inv);
+      const float p = 3.f * cd + 4.5f * cd * (2.f * cu + cd) - 1.5f * dd;
+      post[q] = g[q] + upd[q] + L::w[q] * rho * p;
+    });
+  } else {
+#pragma unroll
+    for (int q = 0; q < L::Q; ++q) post[q] = g[q] + upd[q];
+  }
+}
+
 template <class L, int P>
 struct WideCfg {
   using WL = WideLayout<L::Q, P>;
@@ -527,7 +569,7 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
       float F3[3] = {0.f, 0.f, 0.f};
       if (Fc.kind != 0) body_force(Fc, G, t.x, t.y, t.z, F3);
       float post[Q];
-      finish_collision<L>(g, upd, rho, u, F3, Fc.kind != 0, post);
+      finish_wide<L>(g, upd, rho, u, F3, Fc.kind != 0, post);
       if (valid && t.active) store_rows<L>(dst, row_offsets(G, Q, t.b, t.y, t.z), t, post);
     }
     wave_lds_sync();

@@ -430,3 +430,38 @@ def test_wide_step_16bit_blocks(lbm, lat, shape, batch, force, prec):
     gap, eff = np.linalg.norm(got - want), np.linalg.norm(want - exact)
     print(f"{lat} {shape} x{batch} {prec}: |gpu - emulated| / rounding effect {gap / eff:.2e}")
     assert gap < 0.5 * eff
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("lat,shape,batch,force", [
+    ("D2Q9", (1, 16, 126), 128, 0),
+    ("D2Q9", (1, 16, 126), 128, 1),
+    ("D3Q19", (8, 8, 62), 64, 0),
+    ("D3Q19", (8, 8, 62), 64, 2),
+])
+def test_wide_step_kernels_same_bits(lbm, lat, shape, batch, force, prec):
+    """The two kernels of the 16-bit step, by row items and by blocks of 64
+    nodes, against each other, two steps: the fields of a large batch advanced
+    together and one by one.  On 256 compute units the whole batch has 4096
+    ragged row items (two per wavefront) and some 254,000 nodes, 7.8 blocks
+    per place for one: row items by a factor of 1.3 in the rule; a field
+    alone (32 or 64 items, at most 63 blocks) runs by blocks by a factor of 2."""
+    nz, ny, nx = shape
+    kw = {1: dict(force_kind=1, force_amp=1e-3, force_k=1),
+          2: dict(force_kind=2, force_amp=1e-3, force_k=1)}.get(force, {})
+    theta = dev(inputs.glorot_params_net(inputs.net_widths(9 if lat == "D2Q9" else 19, 0, "paper"),
+                                         seed=7))
+
+    def lattice(n):
+        return lbm.Lattice(lib_config(oracle.Config(
+            lattice=lat, nx=nx, ny=ny, nz=nz, batch=n, tau=0.55, hidden=300, net="paper",
+            out_scale=0.25, **kw), prec))
+
+    A = dev(to_shifted(random_state(oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch,
+                                                  tau=0.55), 76, scale=0.03), lat))
+    L, one = lattice(batch), lattice(1)
+    full = L.step(A, theta, 2)
+    for b in range(0, batch, 7):
+        assert torch.equal(one.step(A[b:b + 1], theta, 2), full[b:b + 1]), b
+    L.close()
+    one.close()
