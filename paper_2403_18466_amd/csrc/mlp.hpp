@@ -122,9 +122,10 @@ __device__ inline f4 mma_pair(f4 acc, typename Frag<P>::T a0, typename Frag<P>::
 // hardware; across the two shapes it is not, and the compiler inserts no
 // wait: issued back to back (or with one other product between), the second
 // one reads a stale accumulator (a chain of both over ones was wrong in every
-// result).  16 wait states cover the eight passes of the first product.
-// Chains with at least three other products between, whose sixteen clocks each
-// cover it, need no call.
+// result).  Twelve wait states are enough: this call waits sixteen, and three
+// other products between, of four each, need no call.  Where the distance
+// rests on such products, scheduling barriers between them keep their order:
+// the scheduler may otherwise take one of the three out of the way.
 __device__ inline void mma_shape_wait(f4& acc) { asm volatile("s_nop 15" : "+v"(acc)); }
 
 // acc += sum over NC input chunks.

@@ -491,6 +491,9 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
                       if constexpr (P != P_F32 && GT * NT < 4) mma_shape_wait(acc[j][n]);
                       acc[j][n] = mma_chunk<P>(acc[j][n], f.a0, h1[WL::K2 - 1][n]);
                     }
+                    // (the order across the two shapes is fixed: the distance
+                    // of four needs it, see mma_shape_wait)
+                    if constexpr (P != P_F32 && k >= NP - 1) __builtin_amdgcn_sched_barrier(0);
                   }
                   if constexpr (u == U2 - 1) {
 #pragma unroll
@@ -542,6 +545,7 @@ __global__ __launch_bounds__(512) void wide_step_kernel(const float* __restrict_
                     if constexpr (P != P_F32 && WL::T4 * NT < 4) mma_shape_wait(acc[t4][n]);
                     acc[t4][n] = mma_chunk<P>(acc[t4][n], f.a0, h3[WL::K4 - 1][n]);
                   }
+                  if constexpr (P != P_F32 && k >= NP - 1) __builtin_amdgcn_sched_barrier(0);
                 }
                 if constexpr (k == KU - 1) {
                   const int row = 16 * t4 + 4 * lg;
