@@ -18,6 +18,7 @@
 #include "kernels_ref.hpp"
 #include "lbm.h"
 #include "wide.hpp"
+#include "wide_rule.hpp"
 #include "wide_step16.hpp"
 #include "wide_adj16.hpp"
 #include "wide_bwd.hpp"
@@ -223,22 +224,6 @@ std::vector<int> wide_index_p(int prec, bool blocks, int& packed_bytes) {
   return wide_index<Q, P_BF16>();
 }
 
-// Which kernel runs the 16-bit wide step.  Both have a unit of work that
-// fills the chip once: eight 64-node row items per compute unit in 31 us for
-// wide_step_kernel, two blocks of 64 nodes per compute unit in 10 us (and 4
-// us of start) for wide_step16_kernel.  So the blocks win on small grids and
-// where rows are no multiple of 64 (D3Q19 bf16, row items / blocks: 32^3 33.5 /
-// 15.1 us, 48^3 64.9 / 37.0, 56^3 66.1 / 55.9, 80^3 208 / 154), the row items,
-// whose weights feed eight times the nodes per read, on the large regular ones
-// (64^3 66.1 / 81.0 us, 256^3 3.93 / 5.15 ms).
-bool wide_by_blocks(const lbm_config& c, int ncu) {
-  const long long nodes = (long long)c.batch * c.nx * c.ny * c.nz;
-  const long long items = (long long)c.batch * ((c.nx + 63) / 64) * c.ny * c.nz;
-  const long long rounds_items = (items + 8LL * ncu - 1) / (8LL * ncu);
-  const long long rounds_blocks = ((nodes + 63) / 64 + 2LL * ncu - 1) / (2LL * ncu);
-  return 10 * rounds_blocks + 4 < 31 * rounds_items;
-}
-
 lbm_status validate(const lbm_config* c) {
   if (!c) return fail(LBM_ERR_INVALID, "config is null");
   if (c->lattice != LBM_D2Q9 && c->lattice != LBM_D3Q19)
@@ -418,16 +403,13 @@ lbm_status launch_wide(lbm_ctx* ctx, const float* Ain, float* Aout, hipStream_t 
   const int prec = prec_of(c.mlp_prec);
   hipError_t e;
   if (!ctx->wide_blocks) {
-    using C = WideCfg<L, P_F32>;  // (wavefronts per workgroup, the same for every precision)
-    int nxc = (G.nx + 63) / 64;
-    long long nitems = (long long)nxc * G.ny * G.nz * G.batch;
+    static_assert(kWideItemWaves == WideCfg<L, P_F32>::WAVES &&
+                      kWideItemWaves == WideCfg<L, P_BF16>::WAVES,
+                  "wavefronts per workgroup");
+    const int nxc = (G.nx + 63) / 64;
+    const long long nitems = wide_row_items(G.batch, G.nx, G.ny, G.nz);
     if (nitems >= (1LL << 31)) return fail(LBM_ERR_INVALID, "too many work items");
-    // one workgroup of 8 wavefronts per compute unit (the LDS holds one)
-    long long nb = ctx->ncu;
-    long long cap = (nitems + C::WAVES - 1) / C::WAVES;
-    if (nb > cap) nb = cap;
-    if (nb >= 16) nb -= nb % 8;
-    const long long per = (nitems + nb * C::WAVES - 1) / (nb * C::WAVES);
+    const auto [nb, per] = wide_item_launch(nitems, ctx->ncu);
     e = wide_step_launch(L::Q == 19, prec, (unsigned)nb, s, Ain, Aout, ctx->wide_packed, G,
                          force_of(ctx), (float)c.rho0, (float)(1.0 / c.tau),
                          (float)(c.out_scale / c.tau), (int)per, (int)nitems, nxc);
@@ -664,7 +646,8 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
   }
   if (cfg->hidden != 0 && cfg->net == LBM_NET_LEAKY_300_300_100) {
     int pbytes = 0;
-    ctx->wide_blocks = cfg->mlp_prec != LBM_MLP_FP32 && wide_by_blocks(*cfg, ctx->ncu);
+    ctx->wide_blocks = cfg->mlp_prec != LBM_MLP_FP32 &&
+                       wide_by_blocks(cfg->batch, cfg->nx, cfg->ny, cfg->nz, ctx->ncu);
     std::vector<int> idx = cfg->lattice == LBM_D2Q9
                                ? wide_index_p<9>(cfg->mlp_prec, ctx->wide_blocks, pbytes)
                                : wide_index_p<19>(cfg->mlp_prec, ctx->wide_blocks, pbytes);

@@ -11,15 +11,15 @@
 //
 // Why this split.  Its unit of work is 64 nodes per workgroup, two workgroups
 // per compute unit, against 512 nodes for the kernel of wide.hpp, which leaves
-// three quarters of the chip idle on a 32^3 grid: 33.5 -> 15.1 us there (D3Q19
-// bf16), 48^3 64.9 -> 37.0 us.  A weight fragment feeds four matrix
+// three quarters of the chip idle on a 32^3 grid: 29.4 -> 12.5 us there (D3Q19
+// bf16), 48^3 62.7 -> 35.0 us.  A weight fragment feeds four matrix
 // instructions (64 nodes) and an activation fragment five; the kernel of
 // wide.hpp feeds sixteen and two, with the weights shared through LDS, and is
-// the faster one where its units fill the chip (256^3 3.93 against 5.15 ms;
-// 128 nodes per workgroup of eight wavefronts here measured 5.06).  What bounds a
-// block is the sum of its phases: per 64 nodes 4,900 clocks of matrix
-// instructions per wavefront, about 700 VALU instructions and 430 KB through
-// LDS, between four barriers that two workgroups only partly overlap.
+// the faster one where its units fill the chip (256^3 3.93 against 5.15 ms; 128
+// nodes per workgroup of eight wavefronts here measured 5.06): wide_rule.hpp.
+// What bounds a block is the sum of its phases: per 64 nodes 4,900 clocks of
+// matrix instructions per wavefront, about 700 VALU instructions and 430 KB
+// through LDS, between four barriers that two workgroups only partly overlap.
 //
 // The node work of block k (gather, network input, and at the end BGK part,
 // projection, force and store) is done by wavefront k % 4, one node per
