@@ -63,6 +63,7 @@
 #include "kernels_bwd.hpp"
 #include "wide.hpp"
 #include "wide_bwd.hpp"
+#include "wide_rule.hpp"
 
 namespace lbm {
 
@@ -106,6 +107,7 @@ struct WideAdj {
   // record blocks
   static constexpr int RX0 = 0, RDY = 1, RH1 = 2, RH2 = 12, RH3 = 22, RZ3 = 26, RZ2 = 30, RZ1 = 40,
                        NREC = 50;
+  static_assert(NREC * 1024 == 16 * kWideRecordBytes, "bytes per node");
   // gradient tiles of a partial slab (256 floats each): dW2 (19 x 19), dW3 (7
   // x 19), dW1 transposed (X0 x dZ1: 2 x 19), dW4 (2 x 7)
   static constexpr int G2 = 0, G3 = G2 + 361, G1 = G3 + 133, G4 = G1 + 38, NG = G4 + 14;
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void wide_adj_data_kernel(
 // Bound by the read of the records.  Ten smaller sets (84 blocks for fifty)
 // with a barrier that waited for every load, one step in flight: 29 us at
 // 32^3, 183 at 60 x 64 x 52; four sets and four steps in flight 23 and 175;
-// with non-temporal loads 103 (see the rule at the launch).
+// with non-temporal loads 103 (see wide_adj_ranges).
 // ---------------------------------------------------------------------------
 constexpr int kWideSets = 4;
 
@@ -617,7 +619,7 @@ __device__ __forceinline__ void wide_adj_weights(const unsigned char* __restrict
 }
 
 // grid: sets x splits; split k covers steps [k per, k per + per) of 32 nodes
-// and writes slab k.
+// and writes slab k (zeros if there are none left for it).
 template <int Q, int P, bool NT>
 __global__ __launch_bounds__(512) void wide_adj_weight_kernel(
     const unsigned char* __restrict__ rec, float* __restrict__ part, int nsteps, int per, int nsplit) {

@@ -3,6 +3,7 @@
 
 #include "wide_adj16.hpp"
 #include "wide_bwd.hpp"
+#include "wide_rule.hpp"
 
 namespace lbm {
 
@@ -115,24 +116,9 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
   const size_t rec_bytes = (size_t)l.Np / 16 * (AJ::NREC * 1024), slab = (size_t)AJ::NG * 1024;
   unsigned char* rec = static_cast<unsigned char*>(ws);
   float* part = reinterpret_cast<float*>(rec + rec_bytes);
-  // Node ranges of the weight gradients, four workgroups each, and the cache
-  // policy of the records.  Below the last-level cache's 256 MB (less what
-  // the fields need) the records are read back from it, and 32 ranges (half
-  // of the chip) read as fast as more while their slabs cost less to write
-  // and sum: D3Q19 bf16, whole adjoint, 32 ranges / 64: 32^3 62 / 66 us, 40^3
-  // (205 MB) 99 / 115 us; with the non-temporal policy 69 and 110 us.  Above
-  // it 64 ranges, one workgroup per compute unit, and non-temporal accesses:
-  // 44^3 (273 MB) 135 us (149 without, 144 with 32 ranges), 60 x 64 x 52 282 us
-  // (361; 301).  At least eight steps of 32 nodes per range on the small
-  // grids.
-  const bool nt = rec_bytes > ((size_t)224 << 20);
+  const bool nt = wide_adj_streams(l.Np);
   const int nsteps = (int)(l.Np / 32);
-  long long room = (long long)((l.total - rec_bytes) / slab), ns = (nsteps + 7) / 8;
-  if (ns > (nt ? 64 : 32)) ns = nt ? 64 : 32;
-  if (ns > room) ns = room;
-  if (ns > 8) ns -= ns % 8;
-  const int per = (int)((nsteps + ns - 1) / ns);
-  const int nsplit = (nsteps + per - 1) / per;
+  const WideAdjRanges r = wide_adj_ranges(l.Np, (long long)((l.total - rec_bytes) / slab));
 
   if (pack) {
     hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((AJ::nw + W::nb + 255) / 256), dim3(256), 0, s,
@@ -140,9 +126,9 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
     WB_CHECK(hipGetLastError());
   }
   WB_CHECK((nt ? run16_launch<L, P, true> : run16_launch<L, P, false>)(
-      s, A, lam1, lam0, packed, rec, part, G, Fc, rho0, omega, knn, l.Np, nsteps, per, nsplit));
-  hipLaunchKernelGGL(wide_adj_reduce_kernel<L::Q>, dim3(AJ::NG), dim3(256), 0, s, part, nsplit,
-                     dtheta);
+      s, A, lam1, lam0, packed, rec, part, G, Fc, rho0, omega, knn, l.Np, nsteps, r.per, r.nsplit));
+  hipLaunchKernelGGL(wide_adj_reduce_kernel<L::Q>, dim3(AJ::NG), dim3(256), 0, s, part,
+                     r.nsplit, dtheta);
   return hipGetLastError();
 }
 

@@ -465,3 +465,27 @@ def test_wide_step_kernels_same_bits(lbm, lat, shape, batch, force, prec):
         assert torch.equal(one.step(A[b:b + 1], theta, 2), full[b:b + 1]), b
     L.close()
     one.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+def test_wide_adjoint_16bit_128_ranges(lbm, prec):
+    """373,248 nodes, 128 node ranges, the last one empty.  Against its fields
+    one by one, as test_wide_adjoint_16bit_beyond_cache: lam the same bits,
+    dtheta the same sums in another order, bar 1e-5."""
+    cfg = dict(lattice="D3Q19", nx=24, ny=24, nz=18, tau=0.55, hidden=300, net="paper",
+               out_scale=0.25)
+    L = lbm.Lattice(lib_config(oracle.Config(batch=36, **cfg), prec))
+    one = lbm.Lattice(lib_config(oracle.Config(batch=1, **cfg), prec))
+    theta = dev(inputs.glorot_params_net(inputs.net_widths(19, 0, "paper"), seed=7))
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    A = torch.randn(L.cfg.state_shape, generator=gen, device="cuda") * 0.03
+    lam1 = torch.randn(L.cfg.state_shape, generator=gen, device="cuda")
+    lam, dth = L.step_backward(A, theta, lam1)
+    sums = torch.zeros(L.n_param, dtype=torch.float64, device="cuda")
+    for b in range(36):
+        l, d = one.step_backward(A[b:b + 1], theta, lam1[b:b + 1])
+        assert torch.equal(lam[b:b + 1], l), b
+        sums += d
+    assert rel_l2(host(dth), host(sums)) < 1e-5
+    L.close()
+    one.close()
