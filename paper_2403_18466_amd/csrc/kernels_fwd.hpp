@@ -931,20 +931,6 @@ __attribute__((amdgpu_waves_per_eu(StepLds<L, H, M>::min_waves(P, FORCED)))) voi
   }
 }
 
-// Workgroups for a persistent kernel: as many as fit on the chip at once
-// (occ per compute unit), no more than there are work units, a multiple of
-// the 8 XCDs when large.
-inline unsigned persistent_grid(int ncu, int occ, long long units_per_block_min,
-                                long long units) {
-  if (occ < 1) occ = 1;
-  long long want = (long long)ncu * occ;
-  long long cap = (units + units_per_block_min - 1) / units_per_block_min;
-  long long nb = want < cap ? want : cap;
-  if (nb >= 16) nb -= nb % 8;
-  if (nb < 1) nb = 1;
-  return (unsigned)nb;
-}
-
 // Launch of the learned-collision step for (lattice, H, precision, forcing),
 // defined in nlbm_fwd.hip with the rule for the work items: a persistent grid.
 hipError_t nlbm_fwd_launch(bool d3q19, int hidden, int prec, bool forced, int ncu, hipStream_t s,

@@ -5,17 +5,18 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels_fwd.hpp"
+#include "step_rule.hpp"
 
 namespace lbm {
 
 namespace {
 
-// Launches the instance for work items of form M; with rounds > 0 only where
-// that gives a wavefront at most so many items (else launched stays false).
+// Launches the instance for work items of form M; with halves > 0 only where
+// there are at most halves / 2 items per wavefront (else launched stays false).
 template <class L, int H, int P, bool FORCED, int M>
 hipError_t fwd_items(int ncu, hipStream_t s, const float* Ain, float* Aout, const float* theta,
                      Grid G, Force Fc, float rho0, float omega, float knn, int nitems, int nxc,
-                     int rounds, bool& launched) {
+                     int halves, bool& launched) {
   const auto kernel = nlbm_step_kernel<L, H, P, FORCED, M>;
   constexpr int wb = StepLds<L, H, M>::waves_per_block(P, FORCED);
   int occ = 1;  // (FLAT16: no more than one workgroup per compute unit)
@@ -23,7 +24,7 @@ hipError_t fwd_items(int ncu, hipStream_t s, const float* Ain, float* Aout, cons
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 64 * wb, 0);
     if (e != hipSuccess) return e;
   }
-  launched = rounds == 0 || nitems <= (long long)rounds * ncu * occ * wb;
+  launched = halves == 0 || 2LL * nitems <= (long long)halves * ncu * occ * wb;
   if (!launched) return hipSuccess;
   hipLaunchKernelGGL(kernel, dim3(persistent_grid(ncu, occ, wb, nitems)), dim3(64 * wb), 0, s,
                      Ain, Aout, theta, G, Fc, rho0, omega, knn, nitems, nxc,
@@ -37,10 +38,10 @@ hipError_t fwd_items(int ncu, hipStream_t s, const float* Ain, float* Aout, cons
 // time is then one wavefront's chain: the staging of the weights, the loads,
 // four dependent network evaluations one after the other, the stores.  In
 // workgroups of four while one per compute unit holds all items, else of
-// eight (fewer stage the weights) while a wavefront gets at most two.  us
-// per step, 64 / 16 nodes: D2Q9 64^2 fp32 H = 32 8.2 / 5.2, bf16 H = 64 13.2
-// / 6.7, 256^2 13.8 / 9.3, 512 x 256 14.2 / 12.5 (two items each; at four,
-// 512^2, 14.8 / 18.7); D3Q19 bf16 16^3 15.6 / 8.1, 32^3 16.1 / 8.9.
+// eight (fewer stage the weights).  us per step, 64 / 16 nodes: D2Q9 64^2 fp32
+// H = 32 8.2 / 5.2, bf16 H = 64 13.2 / 6.7, 256^2 13.8 / 9.3; D3Q19 bf16 16^3
+// 15.6 / 8.1, 32^3 16.1 / 8.9.  Up to one, one and a half or two items per
+// wavefront: step_item_halves.
 // All forms give the same bits: the collision's sums have their roundings
 // written out (a network rounded to 16 bits makes 1e-5 of a last-bit
 // difference within ten steps).
@@ -61,8 +62,9 @@ hipError_t fwd_one(int ncu, hipStream_t s, const float* Ain, float* Aout, const 
     return fwd_items<L, H, P, FORCED, FLAT16>(ncu, s, Ain, Aout, theta, G, Fc, rho0, omega, knn,
                                               n16, nxc, 0, launched);
   if (n16 <= 2 * 32 * ncu) {  // (a compute unit holds 32 wavefronts at most)
+    constexpr int halves = step_item_halves(L::Q, H, P == P_F32, FORCED);
     hipError_t e = fwd_items<L, H, P, FORCED, FLAT16W>(ncu, s, Ain, Aout, theta, G, Fc, rho0,
-                                                       omega, knn, n16, nxc, 2, launched);
+                                                       omega, knn, n16, nxc, halves, launched);
     if (launched || e != hipSuccess) return e;
   }
   if (32LL * 64 * nxc >= 33LL * G.nx)
