@@ -133,3 +133,27 @@ def test_mrt_moment_sums_edges(lbm, shape, batch):
     want = oracle.mrt_moment_sums(ocfg, g.astype(np.float32).astype(np.float64),
                                   to_canonical(A1.cpu().numpy().astype(np.float64), "D3Q19"))
     assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("lat,shape", [("D2Q9", (1, 30, 41)), ("D3Q19", (17, 19, 18))])
+@pytest.mark.parametrize("lmax", [3, 17])
+def test_structure_function_orders_agree(lbm, lat, shape, lmax):
+    """The sums of an order do not depend on how many more are asked for (1 to
+    12 sums per separation go through the wavefront's reduction, for one or
+    four separations): the same bits."""
+    nz, ny, nx = shape
+    L = lbm.Lattice(lbm.Config(lattice=lat, nx=nx, ny=ny, nz=nz))
+    u = torch.from_numpy(np.random.default_rng(96).normal(0, 0.05, (1, L.cfg.D, nz, ny, nx))
+                         .astype(np.float32)).cuda()
+    ws = torch.empty(lbm.lbm_structure_functions_workspace_bytes(L.ctx, lmax, 8) // 8,
+                     dtype=torch.float64, device="cuda")
+    got = {}
+    for pmax in range(1, 9):
+        S, Sa = (torch.full((pmax, lmax), float("nan"), dtype=torch.float64, device="cuda")
+                 for _ in range(2))
+        lbm.lbm_structure_functions(L.ctx, L.cfg, u, lmax, pmax, S, Sa, ws)
+        got[pmax] = S.cpu(), Sa.cpu()
+    for pmax in range(1, 8):
+        for a, b in zip(got[pmax], got[8]):
+            assert torch.equal(a, b[:pmax]), pmax
+    L.close()
