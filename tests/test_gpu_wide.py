@@ -489,3 +489,28 @@ def test_wide_adjoint_16bit_128_ranges(lbm, prec):
     assert rel_l2(host(dth), host(sums)) < 1e-5
     L.close()
     one.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("lat,shape,batch", [("D2Q9", (1, 5, 13), 1), ("D3Q19", (33, 32, 33), 1)])
+def test_wide_16bit_repeats(lbm, lat, shape, batch, prec):
+    """Every one of 300 repeats of the step by blocks and of 100 of the adjoint
+    gives the bits of the first (a race on the activations in LDS or on the
+    next block's populations would show in some of them)."""
+    nz, ny, nx = shape
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25)
+    L = lbm.Lattice(lib_config(ocfg, prec))
+    th = dev(inputs.glorot_params_net(inputs.net_widths(ocfg.Q, 0, "paper"), seed=7))
+    A = dev(to_shifted(random_state(ocfg, 75, scale=0.03), lat))
+    lam1 = dev(to_shifted(random_state(ocfg, 78, scale=1.0), lat))
+    out, (lam, dth) = L.step(A, th, 1), L.step_backward(A, th, lam1)
+    differs = torch.zeros(3, dtype=torch.int64, device="cuda")
+    for _ in range(300):
+        differs[0] += (L.step(A, th, 1) != out).any()
+    for _ in range(100):
+        l, d = L.step_backward(A, th, lam1)
+        differs[1] += (l != lam).any()
+        differs[2] += (d != dth).any()
+    assert differs.tolist() == [0, 0, 0]
+    L.close()
