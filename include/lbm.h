@@ -240,10 +240,10 @@ lbm_status lbm_shift(lbm_ctx* ctx, const float* src, float* dst, int32_t directi
  * for the per-workgroup partial parameter gradients, which are summed in a
  * fixed order (the result is bit-reproducible).  dtheta may be null only
  * when hidden == 0.  lam_n must not alias lam_n1 or A_n.
- * With LBM_NET_LEAKY_300_300_100 the adjoint runs as dense products over the
- * node dimension and keeps every hidden activation in the workspace (about
- * 6 KB per node in bf16/fp16, 12 KB in fp32: meant for training grids such
- * as 32^3 - 64^3); the weights are repacked from theta by the call.  Not
+ * With LBM_NET_LEAKY_300_300_100 the adjoint keeps every hidden activation in
+ * the workspace (3.2 KB per node in bf16/fp16 and at most 72 MB more, 12 KB
+ * per node in fp32: meant for training grids such as 32^3 - 64^3); the
+ * weights are repacked from theta by the call.  Not
  * implemented for LBM_COLLISION_SMAGORINSKY (LBM_ERR_UNSUPPORTED). */
 lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
                              const float* lam_n1, float* lam_n, float* dtheta, void* ws,
@@ -260,8 +260,9 @@ lbm_status lbm_step_backward(lbm_ctx* ctx, const float* A_n, const float* theta,
  * enqueued: this covers plain BGK and every tanh network on grids of any
  * size (their partials depend only on the number of compute units and
  * parameters: 6.8 MB at most on 256 compute units), and the SI's network,
- * whose workspace holds every activation of every node (about 6 KB per node
- * in bf16), only on grids of up to about a thousand nodes.  All calls on one
+ * whose workspace holds every activation of every node (3.2 KB per node in
+ * bf16 and a 0.6 MB slab per 256 nodes), only on grids of up to about 1,500
+ * nodes.  All calls on one
  * device share the buffer: calls that may overlap on one device (different
  * streams, or host threads) race and must be ordered by the caller.
  * Arguments, results and other errors as lbm_step_backward, which it

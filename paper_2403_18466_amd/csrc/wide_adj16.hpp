@@ -111,6 +111,7 @@ struct WideAdj {
   // gradient tiles of a partial slab (256 floats each): dW2 (19 x 19), dW3 (7
   // x 19), dW1 transposed (X0 x dZ1: 2 x 19), dW4 (2 x 7)
   static constexpr int G2 = 0, G3 = G2 + 361, G1 = G3 + 133, G4 = G1 + 38, NG = G4 + 14;
+  static_assert(NG * 1024 == kWideSlabBytes, "bytes of a slab");
 };
 
 // theta index of entry e of the packed weights (see WideAdj; -1 is zero),

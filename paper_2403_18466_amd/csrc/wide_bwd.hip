@@ -17,11 +17,13 @@ struct WsLayout {
   size_t dX0, part, total;
 };
 
+long long padded(long long nodes) { return (nodes + 63) / 64 * 64; }
+
 template <int Q>
 WsLayout ws_layout(long long nodes, size_t es) {
   using W = WideBwd<Q>;
   WsLayout l;
-  l.Np = (nodes + 63) / 64 * 64;
+  l.Np = padded(nodes);
   long long ns = l.Np / 512;
   if (ns < 1) ns = 1;
   if (ns > 128) ns = 128;
@@ -101,10 +103,7 @@ hipError_t run16_launch(hipStream_t s, const float* A, const float* lam1, float*
 }
 
 // The 16-bit networks (wide_adj16.hpp): node-tile records at the start of the
-// workspace, then one gradient slab per node range.  The workspace keeps the
-// size of the product chain's layout, which holds every activation twice:
-// the records (3200 bytes per node against 6144) leave room for at least as
-// many slabs.
+// workspace, then one gradient slab per node range.
 template <class L, int P>
 hipError_t run16(hipStream_t s, const float* A, const float* theta, const float* lam1, float* lam0,
                  float* dtheta, void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
@@ -112,21 +111,19 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
   using W = WideBwd<L::Q>;
   using AJ = WideAdj<L::Q>;
   const long long nodes = (long long)G.plane * G.batch;
-  const WsLayout l = ws_layout<L::Q>(nodes, 2);
-  const size_t rec_bytes = (size_t)l.Np / 16 * (AJ::NREC * 1024), slab = (size_t)AJ::NG * 1024;
+  const long long Np = padded(nodes);
   unsigned char* rec = static_cast<unsigned char*>(ws);
-  float* part = reinterpret_cast<float*>(rec + rec_bytes);
-  const bool nt = wide_adj_streams(l.Np);
-  const int nsteps = (int)(l.Np / 32);
-  const WideAdjRanges r = wide_adj_ranges(l.Np, (long long)((l.total - rec_bytes) / slab));
+  float* part = reinterpret_cast<float*>(rec + Np * kWideRecordBytes);
+  const int nsteps = (int)(Np / 32);
+  const WideAdjRanges r = wide_adj_ranges(Np);
 
   if (pack) {
     hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((AJ::nw + W::nb + 255) / 256), dim3(256), 0, s,
                        theta, idx, packed, AJ::nw, W::nb);
     WB_CHECK(hipGetLastError());
   }
-  WB_CHECK((nt ? run16_launch<L, P, true> : run16_launch<L, P, false>)(
-      s, A, lam1, lam0, packed, rec, part, G, Fc, rho0, omega, knn, l.Np, nsteps, r.per, r.nsplit));
+  WB_CHECK((wide_adj_streams(Np) ? run16_launch<L, P, true> : run16_launch<L, P, false>)(
+      s, A, lam1, lam0, packed, rec, part, G, Fc, rho0, omega, knn, Np, nsteps, r.per, r.nsplit));
   hipLaunchKernelGGL(wide_adj_reduce_kernel<L::Q>, dim3(AJ::NG), dim3(256), 0, s, part,
                      r.nsplit, dtheta);
   return hipGetLastError();
@@ -244,8 +241,8 @@ hipError_t run_prec(int prec, hipStream_t s, const float* A, const float* theta,
 }  // namespace
 
 size_t wide_bwd_workspace_bytes(bool d3q19, int prec, long long nodes) {
-  const size_t es = prec == P_F32 ? 4 : 2;
-  return d3q19 ? ws_layout<19>(nodes, es).total : ws_layout<9>(nodes, es).total;
+  if (prec != P_F32) return (size_t)wide_adj_workspace_bytes(padded(nodes));
+  return d3q19 ? ws_layout<19>(nodes, 4).total : ws_layout<9>(nodes, 4).total;
 }
 
 hipError_t wide_bwd_launch(bool d3q19, int prec, hipStream_t s, const float* A,

@@ -51,8 +51,7 @@ inline bool wide_adj_streams(long long Np) {
 // Node ranges of the weight gradients: nsplit of them, four workgroups and one
 // slab each, of `per` steps of 32 nodes (the last ones of fewer, or none: the
 // number stays a multiple of eight where it exceeds eight, so that a range's
-// workgroups share an XCD).  Np: nodes padded to a multiple of 64; room: slabs
-// that the workspace holds.
+// workgroups share an XCD).  Np: nodes padded to a multiple of 64.
 //
 // Records in the cache are read back from it, and 32 ranges (half of the chip)
 // read as fast as more while their slabs cost less to write and sum: D3Q19
@@ -70,14 +69,19 @@ inline bool wide_adj_streams(long long Np) {
 struct WideAdjRanges {
   int per, nsplit;
 };
-inline WideAdjRanges wide_adj_ranges(long long Np, long long room) {
+inline WideAdjRanges wide_adj_ranges(long long Np) {
   const long long nsteps = Np / 32;
   const long long most = !wide_adj_streams(Np) ? 32 : (Np <= 327680 ? 64 : 128);
   long long ns = (nsteps + 7) / 8;
   if (ns > most) ns = most;
-  if (ns > room) ns = room;
   if (ns > 8) ns -= ns % 8;
   return {(int)((nsteps + ns - 1) / ns), (int)ns};
+}
+
+// Its workspace: the records, then the slabs.
+constexpr long long kWideSlabBytes = 546 * 1024;
+inline long long wide_adj_workspace_bytes(long long Np) {
+  return Np * kWideRecordBytes + wide_adj_ranges(Np).nsplit * kWideSlabBytes;
 }
 
 }  // namespace lbm

@@ -514,3 +514,29 @@ def test_wide_16bit_repeats(lbm, lat, shape, batch, prec):
         differs[2] += (d != dth).any()
     assert differs.tolist() == [0, 0, 0]
     L.close()
+
+
+@pytest.mark.parametrize("lat,shape,batch", [
+    ("D2Q9", (1, 3, 5), 1), ("D2Q9", (1, 40, 41), 1), ("D3Q19", (16, 16, 17), 1),
+    ("D3Q19", (32, 32, 32), 1), ("D3Q19", (44, 44, 44), 1), ("D3Q19", (24, 24, 18), 36),
+])
+def test_wide_adjoint_16bit_workspace(lbm, lat, shape, batch):
+    """The workspace holds one record per node (3,200 bytes) and at most 128
+    gradient slabs, and the adjoint stays inside it: bytes behind the stated
+    size keep their values."""
+    nz, ny, nx = shape
+    ocfg = oracle.Config(lattice=lat, nx=nx, ny=ny, nz=nz, batch=batch, tau=0.55, hidden=300,
+                         net="paper", out_scale=0.25)
+    L = lbm.Lattice(lib_config(ocfg, "bf16"))
+    nodes, need = nx * ny * nz * batch, lbm.lbm_workspace_bytes(L.ctx)
+    assert need <= 3200 * (nodes + 63) + 546 * 1024 * min(128, nodes // 256 + 1)
+    ws = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    th = dev(inputs.glorot_params_net(inputs.net_widths(ocfg.Q, 0, "paper"), seed=7))
+    gen = torch.Generator(device="cuda").manual_seed(79)
+    A = torch.randn(L.cfg.state_shape, generator=gen, device="cuda") * 0.03
+    lam1 = torch.randn(L.cfg.state_shape, generator=gen, device="cuda")
+    lam, dth = torch.empty_like(A), torch.zeros_like(th)
+    lbm.lbm_step_backward(L.ctx, L.cfg, A, th, lam1, lam, dth, ws[:need])
+    assert bool((ws[need:] == 0x5A).all())
+    assert bool(torch.isfinite(lam).all()) and bool(torch.isfinite(dth).all())
+    L.close()

@@ -41,10 +41,10 @@ def test_the_faster_kernel_is_chosen(tmp_path):
 
 def test_gradient_ranges(tmp_path):
     """The 16-bit adjoint's node ranges, from one workgroup of nodes to beyond
-    any grid: they cover every step, their slabs fit, their number is a multiple
-    of eight where it exceeds eight, and no float32 sum runs over more nodes than
-    5,120 or, on the largest grids, than a 128th of all -- the lengths of the
-    chain of products that the kernel replaced."""
+    any grid: they cover every step, their number is a multiple of eight where it
+    exceeds eight, no float32 sum runs over more nodes than 5,120 or, on the
+    largest grids, than a 128th of all (the lengths of the chain of products
+    that the kernel replaced), and the workspace is the records and the slabs."""
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no C++ compiler")
@@ -55,20 +55,18 @@ def test_gradient_ranges(tmp_path):
 #include <initializer_list>
 #include "wide_rule.hpp"
 int main() {
-  for (long long Np : {%s})
-    for (long long room : {1, 5, 31, 127, 128, 4000}) {
-      const lbm::WideAdjRanges r = lbm::wide_adj_ranges(Np, room);
-      std::printf("%%lld %%lld %%d %%d\\n", Np, room, r.per, r.nsplit);
-    }
+  for (long long Np : {%s}) {
+    const lbm::WideAdjRanges r = lbm::wide_adj_ranges(Np);
+    std::printf("%%lld %%d %%d %%lld\\n", Np, r.per, r.nsplit, lbm::wide_adj_workspace_bytes(Np));
+  }
 }
 """ % ", ".join(f"{n}LL" for n in sizes))
     subprocess.run([cxx, "-std=c++17", "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
-    assert len(out.splitlines()) == 6 * len(sizes)
+    assert len(out.splitlines()) == len(sizes)
     for line in out.splitlines():
-        Np, room, per, nsplit = map(int, line.split())
+        Np, per, nsplit, nbytes = map(int, line.split())
         assert per >= 1 and per * nsplit >= Np // 32, line
-        assert 1 <= nsplit <= room, line
-        assert nsplit <= 8 or nsplit % 8 == 0, line
-        if room >= 128:
-            assert 32 * per <= max(5120, (Np // 32 + 127) // 128 * 32), line
+        assert 1 <= nsplit <= 128 and (nsplit <= 8 or nsplit % 8 == 0), line
+        assert 32 * per <= max(5120, (Np // 32 + 127) // 128 * 32), line
+        assert nbytes == 3200 * Np + 546 * 1024 * nsplit, line
