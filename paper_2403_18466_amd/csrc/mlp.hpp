@@ -134,10 +134,8 @@ __device__ inline f4 mma_row(f4 acc, const typename Frag<P>::T* w, const typenam
   int c = 0;
 #pragma unroll
   for (; c + 1 < NC; c += 2) acc = mma_pair<P>(acc, w[c], w[c + 1], x[c], x[c + 1]);
-  if constexpr (NC % 2 == 1) {
-    if constexpr (P != P_F32 && NC > 1) mma_shape_wait(acc);
-    acc = mma_chunk<P>(acc, w[NC - 1], x[NC - 1]);
-  }
+  static_assert(P == P_F32 || NC == 1 || NC % 2 == 0, "a chain of two shapes needs mma_shape_wait");
+  if constexpr (NC % 2 == 1) acc = mma_chunk<P>(acc, w[NC - 1], x[NC - 1]);
   return acc;
 }
 
@@ -149,10 +147,8 @@ __device__ inline f4 mma_row_lds(f4 acc, const typename Frag<P>::T* w,
   int c = 0;
 #pragma unroll
   for (; c + 1 < NC; c += 2) acc = mma_pair<P>(acc, w[64 * c], w[64 * (c + 1)], x[c], x[c + 1]);
-  if constexpr (NC % 2 == 1) {
-    if constexpr (P != P_F32 && NC > 1) mma_shape_wait(acc);
-    acc = mma_chunk<P>(acc, w[64 * (NC - 1)], x[NC - 1]);
-  }
+  static_assert(P == P_F32 || NC == 1 || NC % 2 == 0, "a chain of two shapes needs mma_shape_wait");
+  if constexpr (NC % 2 == 1) acc = mma_chunk<P>(acc, w[64 * (NC - 1)], x[NC - 1]);
   return acc;
 }
 

@@ -20,7 +20,7 @@ struct WsLayout {
 long long padded(long long nodes) { return (nodes + 63) / 64 * 64; }
 
 template <int Q>
-WsLayout ws_layout(long long nodes, size_t es) {
+WsLayout ws_layout(long long nodes) {
   using W = WideBwd<Q>;
   WsLayout l;
   l.Np = padded(nodes);
@@ -36,37 +36,37 @@ WsLayout ws_layout(long long nodes, size_t es) {
     return at;
   };
   const size_t N = (size_t)l.Np;
-  l.X0 = take(N * W::D0 * es);
-  l.X0t = take(N * W::D0 * es);
-  l.H1 = take(N * W::D1 * es);
-  l.H1t = take(N * W::D1 * es);
-  l.H2 = take(N * W::D2 * es);
-  l.H2t = take(N * W::D2 * es);
-  l.H3 = take(N * W::D3 * es);
-  l.H3t = take(N * W::D3 * es);
-  l.dY = take(N * W::D4 * es);
-  l.dYt = take(N * W::D4 * es);
-  l.dZ3 = take(N * W::D3 * es);
-  l.dZ3t = take(N * W::D3 * es);
-  l.dZ2 = take(N * W::D2 * es);
-  l.dZ2t = take(N * W::D2 * es);
-  l.dZ1 = take(N * W::D1 * es);
-  l.dZ1t = take(N * W::D1 * es);
+  l.X0 = take(N * W::D0 * sizeof(float));
+  l.X0t = take(N * W::D0 * sizeof(float));
+  l.H1 = take(N * W::D1 * sizeof(float));
+  l.H1t = take(N * W::D1 * sizeof(float));
+  l.H2 = take(N * W::D2 * sizeof(float));
+  l.H2t = take(N * W::D2 * sizeof(float));
+  l.H3 = take(N * W::D3 * sizeof(float));
+  l.H3t = take(N * W::D3 * sizeof(float));
+  l.dY = take(N * W::D4 * sizeof(float));
+  l.dYt = take(N * W::D4 * sizeof(float));
+  l.dZ3 = take(N * W::D3 * sizeof(float));
+  l.dZ3t = take(N * W::D3 * sizeof(float));
+  l.dZ2 = take(N * W::D2 * sizeof(float));
+  l.dZ2t = take(N * W::D2 * sizeof(float));
+  l.dZ1 = take(N * W::D1 * sizeof(float));
+  l.dZ1t = take(N * W::D1 * sizeof(float));
   l.dX0 = take(N * W::D0 * sizeof(float));
   l.part = take((size_t)l.nsplit * W::ngrad * sizeof(float));
   l.total = o;
   return l;
 }
 
-template <int P, int EPI>
+template <int EPI>
 hipError_t gemm(hipStream_t s, const GemmArgs& a, long long M, int N, int splits) {
   dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)splits);
-  hipLaunchKernelGGL((gemm_nt_kernel<P, EPI>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_nt_kernel<EPI>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-GemmArgs args(const void* A, long long lda, const void* B, long long ldb, int M, int N,
-              long long K, void* C, long long ldc) {
+GemmArgs args(const float* A, long long lda, const float* B, long long ldb, int M, int N,
+              long long K, float* C, long long ldc) {
   GemmArgs a{};
   a.A = A;
   a.B = B;
@@ -129,26 +129,25 @@ hipError_t run16(hipStream_t s, const float* A, const float* theta, const float*
   return hipGetLastError();
 }
 
-template <class L, int P>
-hipError_t run(hipStream_t s, const float* A, const float* theta, const float* lam1, float* lam0,
+template <class L>
+hipError_t run32(hipStream_t s, const float* A, const float* theta, const float* lam1, float* lam0,
                float* dtheta, void* ws, const int* idx, unsigned char* packed, Grid G, Force Fc,
                float rho0, float omega, float knn, bool pack) {
   using W = WideBwd<L::Q>;
-  using T = typename OpT<P>::T;
   const long long nodes = (long long)G.plane * G.batch;
-  const WsLayout l = ws_layout<L::Q>(nodes, sizeof(T));
+  const WsLayout l = ws_layout<L::Q>(nodes);
   unsigned char* base = static_cast<unsigned char*>(ws);
-  auto at = [&](size_t off) { return reinterpret_cast<T*>(base + off); };
-  const T* Wp = reinterpret_cast<const T*>(packed);
-  const float* vec = reinterpret_cast<const float*>(packed + (size_t)W::nw * sizeof(T));
+  auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
+  const float* Wp = reinterpret_cast<const float*>(packed);
+  const float* vec = Wp + W::nw;
   const unsigned nb_nodes = (unsigned)((l.Np + 255) / 256);
 
   if (pack) {
-    hipLaunchKernelGGL(wide_bwd_pack_kernel<P>, dim3((W::nw + W::nb + 255) / 256), dim3(256), 0, s,
+    hipLaunchKernelGGL(wide_bwd_pack_kernel<P_F32>, dim3((W::nw + W::nb + 255) / 256), dim3(256), 0, s,
                        theta, idx, packed, W::nw, W::nb);
     WB_CHECK(hipGetLastError());
   }
-  hipLaunchKernelGGL((wide_prep_kernel<L, P>), dim3(nb_nodes), dim3(256), 0, s, A, G, l.Np,
+  hipLaunchKernelGGL(wide_prep_kernel<L>, dim3(nb_nodes), dim3(256), 0, s, A, G, l.Np,
                      at(l.X0), at(l.X0t));
   WB_CHECK(hipGetLastError());
   const int M = (int)l.Np;
@@ -158,23 +157,23 @@ hipError_t run(hipStream_t s, const float* A, const float* theta, const float* l
     a.Ct = at(l.H1t);
     a.ldct = l.Np;
     a.bias = vec + W::fE1;
-    WB_CHECK((gemm<P, EPI_LEAKY>(s, a, M, W::D1, 1)));
+    WB_CHECK((gemm<EPI_LEAKY>(s, a, M, W::D1, 1)));
   }
   {
     GemmArgs a = args(at(l.H1), W::D1, Wp + W::oW2, W::D1, M, W::D2, W::D1, at(l.H2), W::D2);
     a.Ct = at(l.H2t);
     a.ldct = l.Np;
     a.bias = vec + W::fB2;
-    WB_CHECK((gemm<P, EPI_LEAKY>(s, a, M, W::D2, 1)));
+    WB_CHECK((gemm<EPI_LEAKY>(s, a, M, W::D2, 1)));
   }
   {
     GemmArgs a = args(at(l.H2), W::D2, Wp + W::oW3, W::D2, M, W::D3, W::D2, at(l.H3), W::D3);
     a.Ct = at(l.H3t);
     a.ldct = l.Np;
     a.bias = vec + W::fB3;
-    WB_CHECK((gemm<P, EPI_LEAKY>(s, a, M, W::D3, 1)));
+    WB_CHECK((gemm<EPI_LEAKY>(s, a, M, W::D3, 1)));
   }
-  hipLaunchKernelGGL((wide_dy_kernel<L, P>), dim3(nb_nodes), dim3(256), 0, s, A, lam1, G, Fc, rho0,
+  hipLaunchKernelGGL(wide_dy_kernel<L>, dim3(nb_nodes), dim3(256), 0, s, A, lam1, G, Fc, rho0,
                      omega, knn, l.Np, at(l.dY), at(l.dYt));
   WB_CHECK(hipGetLastError());
   // input gradients of the layers, masked by the LeakyReLU derivative
@@ -183,29 +182,29 @@ hipError_t run(hipStream_t s, const float* A, const float* theta, const float* l
     a.Ct = at(l.dZ3t);
     a.ldct = l.Np;
     a.mask = at(l.H3);
-    WB_CHECK((gemm<P, EPI_MASK>(s, a, M, W::D3, 1)));
+    WB_CHECK((gemm<EPI_MASK>(s, a, M, W::D3, 1)));
   }
   {
     GemmArgs a = args(at(l.dZ3), W::D3, Wp + W::oT3, W::D3, M, W::D2, W::D3, at(l.dZ2), W::D2);
     a.Ct = at(l.dZ2t);
     a.ldct = l.Np;
     a.mask = at(l.H2);
-    WB_CHECK((gemm<P, EPI_MASK>(s, a, M, W::D2, 1)));
+    WB_CHECK((gemm<EPI_MASK>(s, a, M, W::D2, 1)));
   }
   {
     GemmArgs a = args(at(l.dZ2), W::D2, Wp + W::oT2, W::D2, M, W::D1, W::D2, at(l.dZ1), W::D1);
     a.Ct = at(l.dZ1t);
     a.ldct = l.Np;
     a.mask = at(l.H1);
-    WB_CHECK((gemm<P, EPI_MASK>(s, a, M, W::D1, 1)));
+    WB_CHECK((gemm<EPI_MASK>(s, a, M, W::D1, 1)));
   }
-  float* dX0 = reinterpret_cast<float*>(base + l.dX0);
+  float* dX0 = at(l.dX0);
   {
     GemmArgs a = args(at(l.dZ1), W::D1, Wp + W::oT1, W::D1, M, W::D0, W::D1, dX0, W::D0);
-    WB_CHECK((gemm<P, EPI_F32>(s, a, M, W::D0, 1)));
+    WB_CHECK((gemm<EPI_F32>(s, a, M, W::D0, 1)));
   }
   // weight gradients: contractions over the nodes, one slab per node range
-  float* part = reinterpret_cast<float*>(base + l.part);
+  float* part = at(l.part);
   struct Wg {
     size_t a, b;
     int m, n, off;
@@ -217,7 +216,7 @@ hipError_t run(hipStream_t s, const float* A, const float* theta, const float* l
     GemmArgs a = args(at(w.a), l.Np, at(w.b), l.Np, w.m, w.n, l.Np, part + w.off, w.n);
     a.kc = l.kc;
     a.slab = W::ngrad;
-    WB_CHECK((gemm<P, EPI_PARTIAL>(s, a, w.m, w.n, l.nsplit)));
+    WB_CHECK((gemm<EPI_PARTIAL>(s, a, w.m, w.n, l.nsplit)));
   }
   hipLaunchKernelGGL(wide_grad_reduce_kernel<L::Q>, dim3((W::nparam + 255) / 256), dim3(256), 0,
                      s, part, l.nsplit, dtheta);
@@ -232,7 +231,7 @@ hipError_t run_prec(int prec, hipStream_t s, const float* A, const float* theta,
                     float* lam0, float* dtheta, void* ws, const int* idx, unsigned char* packed,
                     Grid G, Force Fc, float rho0, float omega, float knn, bool pack) {
   switch (prec) {
-    case P_F32: return run<L, P_F32>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
+    case P_F32: return run32<L>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
     case P_BF16: return run16<L, P_BF16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
     default: return run16<L, P_F16>(s, A, theta, lam1, lam0, dtheta, ws, idx, packed, G, Fc, rho0, omega, knn, pack);
   }
@@ -242,7 +241,7 @@ hipError_t run_prec(int prec, hipStream_t s, const float* A, const float* theta,
 
 size_t wide_bwd_workspace_bytes(bool d3q19, int prec, long long nodes) {
   if (prec != P_F32) return (size_t)wide_adj_workspace_bytes(padded(nodes));
-  return d3q19 ? ws_layout<19>(nodes, 4).total : ws_layout<9>(nodes, 4).total;
+  return d3q19 ? ws_layout<19>(nodes).total : ws_layout<9>(nodes).total;
 }
 
 hipError_t wide_bwd_launch(bool d3q19, int prec, hipStream_t s, const float* A,

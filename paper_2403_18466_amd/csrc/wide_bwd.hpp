@@ -28,9 +28,9 @@
 // gradients.  The matching padded weight columns are zero, so the constant
 // never reaches the next layer.
 //
-// Reduced precision (as in the forward): X0, H1-H3, dY and dZ1-dZ3 and the
-// weights are rounded to the operand format; accumulation and the biases
-// b2, b3 are float32.
+// In the reduced precisions (wide_adj16.hpp, as in the forward) X0, H1-H3, dY and
+// dZ1-dZ3 and the weights are rounded to the operand format; accumulation and
+// the biases b2, b3 are float32.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -105,11 +105,10 @@ __global__ __launch_bounds__(256) void wide_bwd_pack_kernel(const float* __restr
 
 // X0 (node-major [Np][32]) and its transpose ([32][Np]) from the gathered
 // pre-collision populations; rows past the last node are zero.
-template <class L, int P>
+template <class L>
 __global__ __launch_bounds__(256) void wide_prep_kernel(const float* __restrict__ A, Grid G,
-                                                        long long Np,
-                                                        typename OpT<P>::T* __restrict__ X0,
-                                                        typename OpT<P>::T* __restrict__ X0t) {
+                                                        long long Np, float* __restrict__ X0,
+                                                        float* __restrict__ X0t) {
   const long long n = blockIdx.x * 256LL + threadIdx.x;
   if (n >= Np) return;
   const long long total = (long long)G.plane * G.batch;
@@ -122,20 +121,19 @@ __global__ __launch_bounds__(256) void wide_prep_kernel(const float* __restrict_
 #pragma unroll
   for (int k = 0; k < 32; ++k) {
     const float v = n < total ? (k < L::Q ? g[k] : (k == L::Q ? 1.f : 0.f)) : 0.f;
-    X0[n * 32 + k] = to_op<P>(v);
-    X0t[(long long)k * Np + n] = to_op<P>(v);
+    X0[n * 32 + k] = v;
+    X0t[(long long)k * Np + n] = v;
   }
 }
 
 // dY = (s_out / tau) P mu, mu = lam^{n+1}(x) (local read of the pull-shifted
 // adjoint), node-major [Np][32] and transposed.
-template <class L, int P>
+template <class L>
 __global__ __launch_bounds__(256) void wide_dy_kernel(const float* __restrict__ A,
                                                       const float* __restrict__ lam1, Grid G,
                                                       Force Fc, float rho0, float omega, float knn,
-                                                      long long Np,
-                                                      typename OpT<P>::T* __restrict__ dY,
-                                                      typename OpT<P>::T* __restrict__ dYt) {
+                                                      long long Np, float* __restrict__ dY,
+                                                      float* __restrict__ dYt) {
   const long long n = blockIdx.x * 256LL + threadIdx.x;
   if (n >= Np) return;
   const long long total = (long long)G.plane * G.batch;
@@ -153,8 +151,8 @@ __global__ __launch_bounds__(256) void wide_dy_kernel(const float* __restrict__ 
 #pragma unroll
   for (int k = 0; k < 32; ++k) {
     const float v = (n < total && k < L::Q) ? knn * nu[k] : 0.f;
-    dY[n * 32 + k] = to_op<P>(v);
-    dYt[(long long)k * Np + n] = to_op<P>(v);
+    dY[n * 32 + k] = v;
+    dYt[(long long)k * Np + n] = v;
   }
 }
 
@@ -192,32 +190,31 @@ __global__ __launch_bounds__(256) void wide_post_kernel(const float* __restrict_
 // kc) (split over nodes for the weight gradients).
 // ---------------------------------------------------------------------------
 enum GemmEpi {
-  EPI_LEAKY = 0,    // C, Ct = leaky(acc + bias[j]) in the operand type
-  EPI_MASK = 1,     // C, Ct = acc * leaky'(mask[i][j]) in the operand type
-  EPI_F32 = 2,      // Cf = acc (float32)
-  EPI_PARTIAL = 3,  // Cf[z][i][j] = acc (float32), one slab per K range
+  EPI_LEAKY = 0,    // C, Ct = leaky(acc + bias[j])
+  EPI_MASK = 1,     // C, Ct = acc * leaky'(mask[i][j])
+  EPI_F32 = 2,      // C = acc
+  EPI_PARTIAL = 3,  // C[z][i][j] = acc, one slab per K range
 };
 
 struct GemmArgs {
-  const void* A;
-  const void* B;
+  const float* A;
+  const float* B;
   long long lda, ldb;
   int M, N;
   long long K, kc;
-  void* C;
-  void* Ct;
+  float* C;
+  float* Ct;
   long long ldc, ldct;
   const float* bias;
-  const void* mask;
+  const float* mask;
   long long slab;  // EPI_PARTIAL: elements between consecutive K-range slabs
 };
 
 // Epilogue of a wavefront's 32 x 32 block at (ib, jb); D layout: lane
 // (lg, li) holds rows 4 lg + r, column li of each 16 x 16 tile.
-template <int P, int EPI>
+template <int EPI>
 __device__ inline void gemm_epilogue(const GemmArgs& a, const f4 (&acc)[2][2], int ib, int jb,
                                      int lg, int li) {
-  using T = typename OpT<P>::T;
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -233,35 +230,33 @@ __device__ inline void gemm_epilogue(const GemmArgs& a, const f4 (&acc)[2][2], i
           v += a.bias[j];
           v = v > 0.f ? v : kLeakySlope * v;
         } else if constexpr (EPI == EPI_MASK) {
-          const float m = (float)static_cast<const T*>(a.mask)[(long long)i * a.ldc + j];
+          const float m = a.mask[(long long)i * a.ldc + j];
           v = m > 0.f ? v : kLeakySlope * v;
         }
         if constexpr (EPI == EPI_LEAKY || EPI == EPI_MASK) {
-          static_cast<T*>(a.C)[(long long)i * a.ldc + j] = to_op<P>(v);
-          if (a.Ct) static_cast<T*>(a.Ct)[(long long)j * a.ldct + i] = to_op<P>(v);
+          a.C[(long long)i * a.ldc + j] = v;
+          if (a.Ct) a.Ct[(long long)j * a.ldct + i] = v;
         } else if constexpr (EPI == EPI_F32) {
-          static_cast<float*>(a.C)[(long long)i * a.ldc + j] = v;
+          a.C[(long long)i * a.ldc + j] = v;
         } else {
-          static_cast<float*>(a.C)[(long long)blockIdx.z * a.slab + (long long)i * a.ldc + j] = v;
+          a.C[(long long)blockIdx.z * a.slab + (long long)i * a.ldc + j] = v;
         }
       }
     }
 }
 
-template <int P, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
-  using T = typename OpT<P>::T;
-  using F = typename Frag<P>::T;
   constexpr int SK = 32 + 8;  // LDS row stride (elements)
-  __shared__ __attribute__((aligned(16))) T As[64 * SK];
-  __shared__ __attribute__((aligned(16))) T Bs[64 * SK];
+  __shared__ __attribute__((aligned(16))) float As[64 * SK];
+  __shared__ __attribute__((aligned(16))) float Bs[64 * SK];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lg = lane >> 4, li = lane & 15;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
   const long long k_begin = (long long)blockIdx.z * a.kc;
   long long k_end = k_begin + a.kc;
   if (k_end > a.K) k_end = a.K;
-  const T* A = static_cast<const T*>(a.A);
-  const T* B = static_cast<const T*>(a.B);
+  const float* A = a.A;
+  const float* B = a.B;
   const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
   f4 acc[2][2];
 #pragma unroll
@@ -276,33 +271,30 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const long long k = k0 + sk + e;
-        As[sr * SK + sk + e] = (ra < a.M && k < k_end) ? A[(long long)ra * a.lda + k] : T(0.f);
-        Bs[sr * SK + sk + e] = (rb < a.N && k < k_end) ? B[(long long)rb * a.ldb + k] : T(0.f);
+        As[sr * SK + sk + e] = (ra < a.M && k < k_end) ? A[(long long)ra * a.lda + k] : 0.f;
+        Bs[sr * SK + sk + e] = (rb < a.N && k < k_end) ? B[(long long)rb * a.ldb + k] : 0.f;
       }
     }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      F af[2], bf[2];
+      f4 af[2], bf[2];
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        f4 va, vb;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          va[r] = (float)As[(wi + 16 * s + li) * SK + 16 * c + 4 * lg + r];
-          vb[r] = (float)Bs[(wj + 16 * s + li) * SK + 16 * c + 4 * lg + r];
+          af[s][r] = As[(wi + 16 * s + li) * SK + 16 * c + 4 * lg + r];
+          bf[s][r] = Bs[(wj + 16 * s + li) * SK + 16 * c + 4 * lg + r];
         }
-        af[s] = to_frag<P>(va);
-        bf[s] = to_frag<P>(vb);
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) acc[s][t] = mma_chunk<P>(acc[s][t], af[s], bf[t]);
+        for (int t = 0; t < 2; ++t) acc[s][t] = mma_chunk<P_F32>(acc[s][t], af[s], bf[t]);
     }
     __syncthreads();
   }
-  gemm_epilogue<P, EPI>(a, acc, i0 + wi, j0 + wj, lg, li);
+  gemm_epilogue<EPI>(a, acc, i0 + wi, j0 + wj, lg, li);
 }
 
 // dtheta[p] += sum over the nsplit slabs (fixed order) of the padded weight
