@@ -121,31 +121,36 @@ std::vector<int> wide_adj_index() {
   using A = WideAdj<Q>;
   using W = WideBwd<Q>;
   std::vector<int> idx((size_t)A::nw + W::nb, -1);
-  auto value = [](int l, int o, int k) -> int {
-    switch (l) {
-      case 0: return o < W::N1 ? (k < Q ? W::pW1 + o * Q + k : (k == Q ? W::pb1 + o : -1)) : -1;
-      case 1: return o < W::N2 && k < W::N1 ? W::pW2 + o * W::N1 + k : -1;
-      case 2: return o < W::N3 && k < W::N2 ? W::pW3 + o * W::N2 + k : -1;
-      case 3: return o < W::N3 && k < Q ? W::pW4 + k * W::N3 + o : -1;
-      case 4: return o < W::N2 && k < W::N3 ? W::pW3 + k * W::N2 + o : -1;
-      case 5: return o < W::N1 && k < W::N2 ? W::pW2 + k * W::N1 + o : -1;
-      default: return o < Q && k < W::N1 ? W::pW1 + k * Q + o : -1;
-    }
+  // entry (o, k) of a layer's matrix: theta[at + o so + k sk] for o < no, k < nk
+  struct Matrix {
+    int no, nk, at, so, sk;
   };
-  for (int w = 0; w < A::NWAVE; ++w) {
-    int f = 0;
-    for (int l = 0; l < A::NL; ++l)
+  const Matrix mat[A::NL] = {{W::N1, Q, W::pW1, Q, 1},         {W::N2, W::N1, W::pW2, W::N1, 1},
+                             {W::N3, W::N2, W::pW3, W::N2, 1}, {W::N3, Q, W::pW4, 1, W::N3},
+                             {W::N2, W::N3, W::pW3, 1, W::N2}, {W::N1, W::N2, W::pW2, 1, W::N1},
+                             {Q, W::N1, W::pW1, 1, Q}};
+  int* out = idx.data();
+  for (int w = 0; w < A::NWAVE; ++w)
+    for (int l = 0; l < A::NL; ++l) {
+      const Matrix m = mat[l];
+      const int tiles = A::TPW[l];
       for (int c = 0; c < A::KC[l]; ++c)
-        for (int j = 0; j < A::TPW[l]; ++j, ++f)
-          for (int lane = 0; lane < 64; ++lane)
-            for (int e = 0; e < 8; ++e) {
-              const int i = lane & 15, k = 32 * c + 8 * (lane >> 4) + e;
-              const int t = A::TPW[l] == 5 ? A::tile5(w, j) : (l == A::NL - 1 ? j : 2 * w + j);
-              const int o = l == A::NL - 1 ? 16 * t + i
-                                           : 32 * (t / 2) + 8 * (i / 4) + 4 * (t % 2) + i % 4;
-              idx[((size_t)(w * A::NFW + f) * 64 + lane) * 8 + e] = value(l, o, k);
+        for (int j = 0; j < tiles; ++j) {
+          const int t = tiles == 5 ? A::tile5(w, j) : (l == A::NL - 1 ? j : 2 * w + j);
+          for (int lane = 0; lane < 64; ++lane, out += 8) {
+            const int i = lane & 15, k = 32 * c + 8 * (lane >> 4);
+            const int o = l == A::NL - 1 ? 16 * t + i
+                                         : 32 * (t / 2) + 8 * (i / 4) + 4 * (t % 2) + i % 4;
+            const int from = m.at + o * m.so + k * m.sk;
+            if (o < m.no && k + 8 <= m.nk) {
+              for (int e = 0; e < 8; ++e) out[e] = from + e * m.sk;
+            } else if (o < m.no) {
+              for (int e = 0; k + e < m.nk; ++e) out[e] = from + e * m.sk;
+              if (l == 0 && k <= Q && Q < k + 8) out[Q - k] = W::pb1 + o;
             }
-  }
+          }
+        }
+    }
   int* v = idx.data() + A::nw;
   for (int j = 0; j < W::D1; ++j) v[W::fE1 + j] = j == W::ONE1 ? -2 : -1;
   for (int j = 0; j < W::D2; ++j) v[W::fB2 + j] = j < W::N2 ? W::pb2 + j : (j == W::ONE2 ? -2 : -1);
