@@ -540,3 +540,55 @@ def test_wide_adjoint_16bit_workspace(lbm, lat, shape, batch):
     assert bool((ws[need:] == 0x5A).all())
     assert bool(torch.isfinite(lam).all()) and bool(torch.isfinite(dth).all())
     L.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("n", [44, 70])
+def test_wide_adjoint_16bit_large_reference(lbm, n, prec):
+    """dtheta where the records leave the cache (44^3, 64 node ranges) and
+    with 128 ranges (70^3), against the same products in float64 with the
+    operands rounded where the kernels round them.  What is left are float32
+    sums (some 1e-6), the operands that they tip to the next 16-bit value (one
+    in a few thousand, each by 2^-9 or 2^-12), and with those, once in a million,
+    the sign of a pre-activation: bar 1e-3, every parameter block on its own."""
+    ocfg = oracle.Config(lattice="D3Q19", nx=n, ny=n, nz=n, tau=0.55, hidden=300, net="paper",
+                         out_scale=0.25)
+    L = lbm.Lattice(lib_config(ocfg, prec))
+    theta = dev(inputs.glorot_params_net(inputs.net_widths(19, 0, "paper"), seed=7))
+    theta += 0.01 * torch.randn(theta.shape, device="cuda",
+                                generator=torch.Generator(device="cuda").manual_seed(80))
+    gen = torch.Generator(device="cuda").manual_seed(81)
+    A = torch.randn(L.cfg.state_shape, generator=gen, device="cuda") * 0.03
+    lam1 = torch.randn(L.cfg.state_shape, generator=gen, device="cuda")
+    _, got = L.step_backward(A, theta, lam1)
+    L.close()
+
+    dt = {"bf16": torch.bfloat16, "fp16": torch.float16}[prec]
+    rnd = lambda t: t.float().to(dt).double()
+    offs = _blocks(19)
+    par = [theta[a:b].double() for a, b in zip(offs, offs[1:] + [theta.numel()])]
+    W1, W2, W3, W4 = (rnd(p).reshape(s) for p, s in
+                      zip(par[::2], ((300, 19), (300, 300), (100, 300), (19, 100))))
+    c = np.array(lbm.lbm_lattice_tables("D3Q19")[0])
+    g = torch.stack([torch.roll(A[0, q], shifts=(int(c[q, 2]), int(c[q, 1]), int(c[q, 0])),
+                                dims=(0, 1, 2)).reshape(-1) for q in range(19)], dim=1)
+    X = rnd(g)
+    act = lambda z: rnd(torch.where(z > 0, z, 0.01 * z))
+    H1 = act(X @ W1.T + rnd(par[1]))
+    H2 = act(H1 @ W2.T + par[3])
+    H3 = act(H2 @ W3.T + par[5])
+    mu = lam1[0].reshape(19, -1).T.double()
+    cd = torch.from_numpy(c.astype(np.float64)).cuda()
+    nu = mu - mu.sum(1, keepdim=True) / 19 - (mu @ cd) @ cd.T / 10
+    dY = rnd(0.25 / 0.55 * nu)
+    back = lambda d, W, H: rnd(d @ W * torch.where(H > 0, 1.0, 0.01))
+    dZ3 = back(dY, W4, H3)
+    dZ2 = back(dZ3, W3, H2)
+    dZ1 = back(dZ2, W2, H1)
+    want = []
+    for d, x in ((dZ1, X), (dZ2, H1), (dZ3, H2), (dY, H3)):
+        want += [(d.T @ x).reshape(-1), d.sum(0)]
+    errs = [((got[a:a + w.numel()].double() - w).norm() / w.norm()).item() for a, w in zip(offs, want)]
+    print(f"{n}^3 {prec}: blocks " + " ".join(f"{e:.1e}" for e in errs))
+    assert sum(w.numel() for w in want) == theta.numel()
+    assert max(errs) < 1e-3
