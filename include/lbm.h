@@ -147,9 +147,9 @@ typedef struct {
  * streams).  With
  * LBM_NET_LEAKY_300_300_100 it also holds the weights in the kernel's
  * fragment order (about 0.3 MB in bf16/fp16, 0.6 MB in fp32, refreshed from
- * theta by every lbm_step call) and its index table (0.6 MB), plus the
- * adjoint's padded W and W^T (0.6 MB in bf16/fp16, 1.1 MB in fp32) and its
- * index table (1.1 MB).  Limit:
+ * theta by every lbm_step call) and its index table (0.6-0.7 MB), plus the
+ * adjoint's weights (0.7 MB in bf16/fp16, 1.1 MB in fp32) and their index
+ * table (1.4 MB; fp32 1.1 MB).  Limit:
  * batch * Q * nx * ny * nz < 2^30 elements (each population array below
  * 4 GiB, the range of the kernels' 32-bit byte offsets).  Returns
  * LBM_ERR_INVALID or LBM_ERR_UNSUPPORTED with the reason in

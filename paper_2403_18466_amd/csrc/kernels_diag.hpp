@@ -94,7 +94,7 @@ struct NodeWalk {
 // 24 in the straightforward form, for 77 us of them at 128^3 and 32
 // separations.  A thread takes LB separations of a node, so that the node's
 // own values and coordinates are read and formed once.  128^3, 32 separations,
-// PM = 6: 168 us (620 us with one separation per thread, all eight powers and
+// PM = 6: 155 us (620 us with one separation per thread, all eight powers and
 // 64-bit divisions).
 template <int D, int PM, int LB>
 __global__ __launch_bounds__(SF_THREADS) void structure_kernel(const float* __restrict__ u, Grid G,
@@ -232,7 +232,7 @@ static constexpr signed char kMrtM[19][19] = {
 // One pass over both states: a thread keeps the 95 sums (190 registers; one
 // wavefront per SIMD, with the next node's 38 loads in flight while this
 // one's moments are formed; M's zeros are skipped at compile time).  128^3:
-// 131 us (bound: 64 us of reading at the rate of a copy, 60 us of VALU
+// 111 us (bound: 64 us of reading at the rate of a copy, 60 us of VALU
 // issue); 1,220 us as a workgroup row per moment, which read both states and
 // formed f_eq and f_ext nineteen times.
 static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void

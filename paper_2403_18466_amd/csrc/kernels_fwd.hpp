@@ -710,8 +710,8 @@ struct StepLds {
   // 16-bit D3Q19 one run one workgroup per compute unit (four wavefronts per
   // SIMD for D2Q9, three for D3Q19), so that the weights are staged once per
   // compute unit and each thread stages a quarter as many of them; the
-  // others run workgroups of 4 (the forced 16-bit D3Q19 instance needs 187
-  // registers per lane, and at three wavefronts per SIMD it would spill)
+  // others run workgroups of 4 (the forced 16-bit D3Q19 instance at H = 64
+  // needs 243 registers per lane, two wavefronts per SIMD)
   static constexpr int waves_per_block(int prec, bool forced) {
     if (M >= FLAT16) return M == FLAT16 ? 4 : 8;
     return (prec == P_F32 || (forced && L::Q == 19)) ? 4 : (L::Q == 19 ? 12 : 16);
@@ -719,9 +719,9 @@ struct StepLds {
 };
 
 // FORCED: the body force of eq. fext is applied (Force::kind != 0).  The
-// unforced instances leave out the force's registers: 108 instead of 120
-// registers per lane for the 16-bit D2Q9 instance, 159 instead of 187 for
-// D3Q19.
+// unforced instances leave out the force's registers: 118 instead of 123
+// registers per lane for the 16-bit D2Q9 instance, 165 instead of 243 for
+// D3Q19 (H = 64).
 template <class L, int H, int P, bool FORCED, int M>
 __global__ __launch_bounds__((64 * StepLds<L, H, M>::waves_per_block(P, FORCED)))
 __attribute__((amdgpu_waves_per_eu(StepLds<L, H, M>::min_waves(P, FORCED)))) void nlbm_step_kernel(
