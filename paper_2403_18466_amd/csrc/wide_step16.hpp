@@ -230,8 +230,9 @@ __global__ __launch_bounds__(256, 2) void wide_step16_kernel(
         constexpr int n = decltype(nc)::value;
 #pragma unroll
         for (int j = 0; j < T; ++j) {
-          // (the last unit accumulates on products of the other shape; with
-          // 4 T products per unit there are 4 T - 1 >= 7 others between)
+          // (the last unit accumulates on products of the other shape: the
+          // barriers keep the node tiles in order, so that at least the 3 T
+          // >= 6 products of the three other tiles stand between)
           static_assert(T >= 2, "distance between products of the two shapes");
           acc[j][n] = mma(ring[s % 3][j], xb[n], acc[j][n], single);
         }

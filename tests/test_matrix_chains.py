@@ -15,8 +15,6 @@ import pytest
 
 from paper_2403_18466_amd import build
 
-OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc()))), "llvm",
-                       "bin", "llvm-objdump")
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -76,7 +74,9 @@ def crossings(lines):
 
 
 def test_products_of_two_shapes_keep_their_distance(tmp_path):
-    if not os.path.exists(OBJDUMP):
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
+    objdump = os.path.join(rocm, "llvm", "bin", "llvm-objdump")
+    if not os.path.exists(objdump):
         pytest.skip("llvm-objdump not found")
     if not os.path.exists(build.LIB):
         build.build()
@@ -84,7 +84,7 @@ def test_products_of_two_shapes_keep_their_distance(tmp_path):
     for i, code in enumerate(code_objects(build.LIB)):
         path = tmp_path / f"{i}.co"
         path.write_bytes(code)
-        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)],
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)],
                               check=True, capture_output=True, text=True).stdout
         for c in crossings(text.splitlines()):
             seen.add(c[0])
